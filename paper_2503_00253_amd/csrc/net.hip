@@ -5,6 +5,7 @@
 //   5 int32  layers (4), input channels (1), hidden channels H, kernel width K, output channels D
 //   float32  parameters in order W1 (H x 1 x K), b1 (H), W2 (H x H x K), b2 (H),
 //            W3 (H x H x K), b3 (H), W4 (D x H x K), b4 (D)
+#include <algorithm>
 #include <cmath>
 #include <cstdio>
 #include <cstring>
@@ -34,9 +35,9 @@ namespace {
 
 // Training workspace (floats): z1 a1 z2 a2 z3 a3 (B H m each), the trunk output y and its gradient
 // gy (B D m), per-system errors and gradient factors (B Q each), loss (1), two gradient buffers
-// (B H m) and the flipped weights (H H K).  Inference: two (B H m) buffers.
+// (B H m) and the weight gradients' partial sums (the widest layer's).  Inference: two (B H m) buffers.
 struct NetWs {
-  float *z[3], *a[3], *y, *gy, *per, *scale, *loss, *g0, *g1, *wt;
+  float *z[3], *a[3], *y, *gy, *per, *scale, *loss, *g0, *g1, *part;
   float *p0, *p1;                // inference ping-pong (FP32)
   __hip_bfloat16 *q0, *q1;       // inference ping-pong (BF16, position-major)
   __hip_bfloat16* wpk[4];        // packed BF16 weights of the four layers
@@ -66,7 +67,14 @@ NetWs carve(const Net& n, int64_t B, int64_t Q, int64_t m, bool training, void* 
     w.loss = take(1);
     w.g0 = take(act);
     w.g1 = take(act);
-    w.wt = take((int64_t)n.H * n.H * n.K);
+    int64_t most = 0;
+    for (int l = 0; l < 4; ++l) {
+      int64_t wo, bo;
+      int ci, co;
+      net_layer(n, l, &wo, &bo, &ci, &co);
+      most = std::max(most, wgrad_part_floats(ci, co, n.K, (int)m, B));
+    }
+    w.part = take(most);
   } else {
     w.p0 = take(act);
     w.p1 = take(act);
@@ -146,13 +154,12 @@ int gradients(const Net& n, const float* X, const float* cq, const float* T, int
     int ci, co;
     net_layer(n, l, &wo, &bo, &ci, &co);
     const float* a_in = (l == 0) ? X : w.a[l - 1];
-    IE_HIP(launch_conv_wgrad(a_in, ci, g, co, n.K, (int)m, B, grads + wo, grads + bo, st));
+    IE_HIP(launch_conv_wgrad(a_in, ci, g, co, n.K, (int)m, B, grads + wo, grads + bo, w.part, st));
     if (l == 0) break;
-    // gradient w.r.t. the input activation a_{l-1}, then through GELU to z_{l-1}
+    // gradient w.r.t. the input activation a_{l-1}, then through GELU to z_{l-1}, in one launch
     float* gin = (l % 2 == 1) ? w.g0 : w.g1;
-    IE_HIP(launch_flip_transpose(n.params + wo, co, ci, n.K, w.wt, st));
-    IE_HIP(launch_conv_fwd(g, co, w.wt, nullptr, ci, n.K, (int)m, B, nullptr, gin, 0, st));
-    IE_HIP(launch_gelu_bwd(gin, w.z[l - 1], B * (int64_t)ci * m, st));
+    IE_HIP(launch_conv_fwd(g, co, n.params + wo, nullptr, ci, n.K, (int)m, B, nullptr, gin, 0, st, /*flip=*/true,
+                           w.z[l - 1]));
     g = gin;
   }
   return 0;

@@ -38,8 +38,12 @@ int net_forward(const Net& n, const float* X, int64_t B, int64_t m, float* Y, vo
 int net_forward_bf16(const Net& n, const float* X, int64_t B, int64_t m, float* Y, void* ws, size_t ws_bytes,
                      hipStream_t st);
 
+// The "same" correlation with W (Cout, Cin, K) in FP32 on MFMA; pre (nullable) keeps the values before
+// GELU.  flip: W is (Cin, Cout, K), applied as W'[o, c, k] = W[c, o, K - 1 - k] (the input gradient);
+// dz (nullable): outputs times GELU'(dz).
 hipError_t launch_conv_fwd(const float* in, int Cin, const float* W, const float* bias, int Cout, int K, int m,
-                           int64_t B, float* pre, float* act, int gelu, hipStream_t st);
+                           int64_t B, float* pre, float* act, int gelu, hipStream_t st, bool flip = false,
+                           const float* dz = nullptr);
 // BF16 inference: packed weights (round_up(Cout, 16) rows of bf16_kd(Cin, K) entries), and the
 // MFMA correlation (inputs (B, Cin, m) FP32 or (B, m, Cin) BF16 with Cin a multiple of 8; outputs
 // (B, m) FP32 when Cout = 1 or (B, m, Cout) BF16).  Cin, Cout <= 64.
@@ -49,10 +53,10 @@ int bf16_opad(int Cout);
 hipError_t launch_pack_weights_bf16(const float* W, int Cout, int Cin, int K, __hip_bfloat16* out, hipStream_t st);
 hipError_t launch_conv_bf16(const void* in, bool in_f32, int Cin, const __hip_bfloat16* Wp, const float* bias, int Cout,
                             int K, int m, int64_t B, void* out, bool out_f32, int gelu, hipStream_t st);
+// Weight and bias gradients of a layer; part holds wgrad_part_floats(...) floats of partial sums.
+int64_t wgrad_part_floats(int Cin, int Cout, int K, int m, int64_t B);
 hipError_t launch_conv_wgrad(const float* a, int Cin, const float* g, int Cout, int K, int m, int64_t B, float* gW,
-                             float* gb, hipStream_t st);
-hipError_t launch_flip_transpose(const float* W, int Cout, int Cin, int K, float* Wt, hipStream_t st);
-hipError_t launch_gelu_bwd(float* g, const float* z, int64_t n, hipStream_t st);
+                             float* gb, float* part, hipStream_t st);
 // The shift head's loss and gradient for B members x Q shifts (cq: Q values c = 1 / (1 + s)):
 // per-system relative L2 errors against T (B x Q x m) into per (B Q), their mean into *mean,
 // the gradient factors into scale (B Q) and dL/dY (B x D x m) into gY.

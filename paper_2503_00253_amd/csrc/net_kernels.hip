@@ -7,6 +7,7 @@
 //   y[b, o, x] = bias[o] + sum_c sum_k W[o, c, k] a[b, c, x + k - K/2].
 //
 // All arithmetic is FP32 (accumulation in FP32, reductions in a fixed order).
+#include <algorithm>
 #include <cmath>
 
 #include "internal.hpp"
@@ -15,8 +16,8 @@ namespace infoesrf {
 
 namespace {
 
-constexpr int kTX = 64;    // positions per block (one per lane)
 constexpr int kCIC = 16;   // input channels staged per chunk
+typedef float nf4 __attribute__((ext_vector_type(4)));
 
 __device__ inline float gelu_f(float z) { return 0.5f * z * (1.0f + erff(z * 0.70710678118654752f)); }
 __device__ inline float gelu_grad_f(float z) {
@@ -25,55 +26,111 @@ __device__ inline float gelu_grad_f(float z) {
   return Phi + z * phi;
 }
 
-// Direct correlation.  Block: 64 positions (lanes) x 4 * CPW output channels (CPW per wave).
-// Input window and weight chunk in LDS; weights are read as wave-uniform broadcasts.
-template <int CPW>
-__global__ __launch_bounds__(256) void k_conv_fwd(const float* __restrict__ in, int Cin, const float* __restrict__ W,
-                                                  const float* __restrict__ bias, int Cout, int K, int m,
-                                                  float* __restrict__ pre, float* __restrict__ act, int gelu) {
+// The correlation as an implicit GEMM on FP32 MFMA (v_mfma_f32_16x16x4_f32: FP32 operands and
+// accumulation): output channels x positions, contracted over input channels four at a time and taps.
+// Block: 64 output channels (16 a wavefront) x 32 positions.  Input channels come in chunks of 16 whose
+// weights and window lie in LDS; the next chunk's values are loaded into registers while this one is
+// multiplied.  LDS strides: a window row of kWinS = 80 words puts the 16 positions x 4 channels of an
+// operand on 64 banks, a weight row of 16 K + 4 words the 16 outputs x 4 channels (K is odd).  32
+// positions a block, so that the smallest training batches (8 members x 1024 positions) still give one
+// block a CU; the LDS reads (3 words a lane for 2 MFMA) then bound it.  8 members x 1024 positions, 64 x
+// 64 channels, 9 taps (604 MFLOP): 46 us with FP32 FMAs, four output channels a wavefront; 18 us so.
+// FLIP: the weights are those of the layer whose input gradient this is, W (Cin, Cout, K), read as
+// W'[o, c, k] = W[c, o, K - 1 - k] (the input gradient of a "same" correlation is the correlation of
+// the output gradient with W').  dz (nullable): the outputs are multiplied by GELU'(dz).
+constexpr int kCX = 32;    // positions per block
+constexpr int kWinS = 80;  // words per window row: at least kCX + 14, 16 (mod 64)
+constexpr int kMaxTaps = 15;
+__host__ __device__ constexpr int conv_row(int K) { return kCIC * K + 4; }
+
+template <int K, bool FLIP>
+__global__ __launch_bounds__(256) void k_conv_mfma(const float* __restrict__ in, int Cin, const float* __restrict__ W,
+                                                   const float* __restrict__ bias, int Cout, int m,
+                                                   float* __restrict__ pre, float* __restrict__ act, int gelu,
+                                                   const float* __restrict__ dz) {
   extern __shared__ float sm[];
-  const int h = K / 2;
-  const int WX = kTX + K - 1;
-  float* win = sm;                      // kCIC x WX
-  float* wts = sm + kCIC * WX;          // (4 CPW) x kCIC x K
-  const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
-  const int x0 = blockIdx.x * kTX;
-  const int o0 = blockIdx.y * 4 * CPW;
+  float* win = sm;                  // kCIC x kWinS
+  float* wts = sm + kCIC * kWinS;   // 64 x conv_row(K)
+  constexpr int h = K / 2, RS = conv_row(K), WX = kCX + K - 1;
+  constexpr int NW = 64 * kCIC * K / 256, NI = (kCIC * WX + 255) / 256;  // weights, window values a thread loads
+  const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
+  const int l16 = lane & 15, lq = lane >> 4;
+  const int x0 = blockIdx.x * kCX;
+  const int o0 = blockIdx.y * 64;
   const int64_t b = blockIdx.z;
   const float* inb = in + b * (int64_t)Cin * m;
-  float acc[CPW];
+  float rw[NW], ri[NI];
+  auto load = [&](int c0) {
 #pragma unroll
-  for (int j = 0; j < CPW; ++j) acc[j] = 0.f;
-  for (int c0 = 0; c0 < Cin; c0 += kCIC) {
-    const int cc = min(kCIC, Cin - c0);
-    __syncthreads();
-    for (int t = threadIdx.x; t < kCIC * WX; t += 256) {
-      const int ci = t / WX, u = t % WX;
-      const int x = x0 - h + u;
-      win[t] = (ci < cc && x >= 0 && x < m) ? inb[(int64_t)(c0 + ci) * m + x] : 0.f;
-    }
-    for (int t = threadIdx.x; t < 4 * CPW * kCIC * K; t += 256) {
-      const int o = t / (kCIC * K), rem = t % (kCIC * K), ci = rem / K, k = rem % K;
-      wts[t] = (o0 + o < Cout && ci < cc) ? W[((int64_t)(o0 + o) * Cin + c0 + ci) * K + k] : 0.f;
-    }
-    __syncthreads();
-    for (int ci = 0; ci < cc; ++ci)
-      for (int k = 0; k < K; ++k) {
-        const float v = win[ci * WX + lane + k];
-#pragma unroll
-        for (int j = 0; j < CPW; ++j) acc[j] = fmaf(wts[((wave * CPW + j) * kCIC + ci) * K + k], v, acc[j]);
+    for (int i = 0; i < NW; ++i) {
+      const int t = tid + 256 * i;
+      float v = 0.f;
+      if (!FLIP) {
+        const int o = t / (kCIC * K), u = t % (kCIC * K);
+        if (o0 + o < Cout && u < (Cin - c0) * K) v = W[((int64_t)(o0 + o) * Cin + c0) * K + u];
+      } else {
+        const int c = t / (64 * K), u = t % (64 * K);
+        if (c0 + c < Cin && u < (Cout - o0) * K) v = W[((int64_t)(c0 + c) * Cout + o0) * K + u];
       }
-  }
-  const int x = x0 + lane;
-  if (x >= m) return;
+      rw[i] = v;
+    }
 #pragma unroll
-  for (int j = 0; j < CPW; ++j) {
-    const int o = o0 + wave * CPW + j;
-    if (o >= Cout) continue;
-    const float z = acc[j] + (bias ? bias[o] : 0.f);
-    const int64_t at = (b * Cout + o) * (int64_t)m + x;
-    if (pre) pre[at] = z;
-    act[at] = gelu ? gelu_f(z) : z;
+    for (int i = 0; i < NI; ++i) {
+      const int t = tid + 256 * i, c = t / WX, u = t % WX, x = x0 - h + u;
+      ri[i] = (c < kCIC && c0 + c < Cin && x >= 0 && x < m) ? inb[(int64_t)(c0 + c) * m + x] : 0.f;
+    }
+  };
+  // a chunk's sums start at zero and are added to the total, which shortens the FP32 chains
+  nf4 tot[2] = {nf4{0.f, 0.f, 0.f, 0.f}, nf4{0.f, 0.f, 0.f, 0.f}};
+  load(0);
+  for (int c0 = 0; c0 < Cin; c0 += kCIC) {
+    __syncthreads();  // the previous chunk's reads are done
+#pragma unroll
+    for (int i = 0; i < NW; ++i) {
+      const int t = tid + 256 * i;
+      if (!FLIP) {
+        wts[(t / (kCIC * K)) * RS + t % (kCIC * K)] = rw[i];
+      } else {
+        const int c = t / (64 * K), u = t % (64 * K);
+        wts[(u / K) * RS + c * K + K - 1 - u % K] = rw[i];
+      }
+    }
+#pragma unroll
+    for (int i = 0; i < NI; ++i) {
+      const int t = tid + 256 * i, c = t / WX;
+      if (c < kCIC) win[c * kWinS + t % WX] = ri[i];
+    }
+    __syncthreads();
+    if (c0 + kCIC < Cin) load(c0 + kCIC);
+    nf4 acc[2] = {nf4{0.f, 0.f, 0.f, 0.f}, nf4{0.f, 0.f, 0.f, 0.f}};
+    const int cq = min(kCIC, (Cin - c0 + 3) & ~3);
+    for (int c = lq; c < cq; c += 4) {
+      const float* wr = wts + (16 * wave + l16) * RS + c * K;
+      const float* ir = win + c * kWinS + l16;
+#pragma unroll
+      for (int k = 0; k < K; ++k) {
+        const float a = wr[k];
+        acc[0] = __builtin_amdgcn_mfma_f32_16x16x4f32(a, ir[k], acc[0], 0, 0, 0);
+        acc[1] = __builtin_amdgcn_mfma_f32_16x16x4f32(a, ir[k + 16], acc[1], 0, 0, 0);
+      }
+    }
+    tot[0] += acc[0];
+    tot[1] += acc[1];
+  }
+  // D register v of lane l: output channel 4 (l / 16) + v of the wavefront's 16, position l % 16
+#pragma unroll
+  for (int t = 0; t < 2; ++t) {
+    const int x = x0 + 16 * t + l16;
+    if (x >= m) continue;
+#pragma unroll
+    for (int v = 0; v < 4; ++v) {
+      const int o = o0 + 16 * wave + 4 * lq + v;
+      if (o >= Cout) continue;
+      const float z = tot[t][v] + (bias ? bias[o] : 0.f);
+      const int64_t at = (b * Cout + o) * (int64_t)m + x;
+      if (pre) pre[at] = z;
+      act[at] = dz ? z * gelu_grad_f(dz[at]) : (gelu ? gelu_f(z) : z);
+    }
   }
 }
 
@@ -84,7 +141,6 @@ __global__ __launch_bounds__(256) void k_conv_fwd(const float* __restrict__ in, 
 // per call to BF16 rows of KD = round_up(K Cp, 32) entries (Cout rounded up to 16 rows, zeros in
 // the padding).  Activations between layers are BF16, position-major (b, x, c).
 typedef __bf16 nbf8 __attribute__((ext_vector_type(8)));
-typedef float nf4 __attribute__((ext_vector_type(4)));
 
 __global__ void k_pack_weights_bf16(const float* __restrict__ W, int Cout, int Cin, int K, int Cp, int KD, int Opad,
                                     __hip_bfloat16* __restrict__ out) {
@@ -167,75 +223,120 @@ __global__ __launch_bounds__(256) void k_conv_bf16(const void* __restrict__ in, 
 }
 
 // Weight gradient of one layer: gW[o, c, k] = sum_{b, x} g[b, o, x] a[b, c, x + k - K/2] and
-// gb[o] = sum_{b, x} g[b, o, x].  Block (o, c-group of 8): threads stride over (b, x) and keep
-// 8 K partial sums; then a fixed-order reduction (wave shuffles, then the four waves).
-__global__ __launch_bounds__(256) void k_conv_wgrad(const float* __restrict__ a, int Cin, const float* __restrict__ g,
-                                                    int Cout, int K, int m, int64_t B, float* __restrict__ gW,
-                                                    float* __restrict__ gb) {
-  constexpr int CG = 8;
-  constexpr int KMAX = 15;
-  __shared__ float red[4][CG * KMAX + 1];
-  const int o = blockIdx.x;
-  const int c0 = blockIdx.y * CG;
-  const int h = K / 2;
-  float acc[CG * KMAX + 1];
+// gb[o] = sum_{b, x} g[b, o, x], as one product per tap on FP32 MFMA (v_mfma_f32_16x16x4_f32, FP32
+// operands and accumulation): output channels x input channels, contracted over positions.  The B m
+// positions come in chunks of kGX of one member; block (s, c-tile, o-group) adds the chunks s, s + nsplit,
+// ... for 64 output channels (16 a wavefront) and 16 input channels, every tap in registers, and writes
+// its partial sums; k_wgrad_reduce adds the nsplit partials in order in FP64.  Sums of 32 positions start
+// at zero and are added to the block's, so the FP32 chains stay short.  The split fills the chip, which one
+// block per (output channel, 8 input channels) did not: 64 x 64 channels, 9 taps, 8 members x 1024
+// positions (604 MFLOP) 570 us before, 22 us and 5 us for the reduction now.  LDS rows are 4 (mod 8) words apart, so the
+// 16 channels x 4 positions of an operand lie on 64 banks.
+constexpr int kGX = 128;
+constexpr int kGS = kGX + 4, kAS = kGX + 20;  // row strides of g and of the window (kGX + 14 at most)
+
+template <int K>
+__global__ __launch_bounds__(256) void k_wgrad_mfma(const float* __restrict__ a, int Cin, const float* __restrict__ g,
+                                                    int Cout, int m, int64_t B, float* __restrict__ part) {
+  extern __shared__ float sm[];
+  float* sg = sm;                // 64 x kGS
+  float* sa = sm + 64 * kGS;     // 16 x kAS
+  constexpr int h = K / 2, WX = kGX + K - 1;
+  const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
+  const int l16 = lane & 15, lq = lane >> 4;
+  const int c0 = blockIdx.y * 16, o0 = blockIdx.z * 64;
+  const int per = (m + kGX - 1) / kGX;          // chunks a member
+  const int64_t chunks = B * per;
+  const bool mine = o0 + 16 * wave < Cout;      // the wavefront has output channels
+  nf4 tot[K], acc[K];
 #pragma unroll
-  for (int j = 0; j < CG * KMAX + 1; ++j) acc[j] = 0.f;
-  const int64_t total = B * (int64_t)m;
-  for (int64_t p = threadIdx.x; p < total; p += 256) {
-    const int64_t b = p / m;
-    const int x = (int)(p % m);
-    const float gv = g[(b * Cout + o) * (int64_t)m + x];
-    acc[CG * KMAX] += gv;
+  for (int k = 0; k < K; ++k) tot[k] = acc[k] = nf4{0.f, 0.f, 0.f, 0.f};
+  float sb = 0.f;
+  auto flush = [&]() {
 #pragma unroll
-    for (int cj = 0; cj < CG; ++cj) {
-      const int c = c0 + cj;
-      if (c >= Cin) break;
-      const float* ar = a + (b * Cin + c) * (int64_t)m;
+    for (int k = 0; k < K; ++k) {
+      tot[k] += acc[k];
+      acc[k] = nf4{0.f, 0.f, 0.f, 0.f};
+    }
+  };
+  for (int64_t ch = blockIdx.x; ch < chunks; ch += gridDim.x) {
+    const int64_t b = ch / per;
+    const int x0 = (int)(ch % per) * kGX;
+    const float* gp = g + (b * Cout + o0) * (int64_t)m;
+    const float* ap = a + (b * Cin + c0) * (int64_t)m;
+    __syncthreads();  // the previous chunk's reads are done
+#pragma unroll 8
+    for (int i = 0; i < 64 * kGX / 256; ++i) {
+      const int t = tid + 256 * i, o = t / kGX, x = x0 + t % kGX;
+      sg[o * kGS + t % kGX] = (o0 + o < Cout && x < m) ? gp[(int64_t)o * m + x] : 0.f;
+    }
+#pragma unroll 5
+    for (int t = tid; t < 16 * WX; t += 256) {
+      const int c = t / WX, u = t % WX, x = x0 - h + u;
+      sa[c * kAS + u] = (c0 + c < Cin && x >= 0 && x < m) ? ap[(int64_t)c * m + x] : 0.f;
+    }
+    __syncthreads();
+    if (!mine) continue;
+    const float* gr = sg + (16 * wave + l16) * kGS + lq;
+    const float* ar = sa + l16 * kAS + lq;
+    const int nx = min(kGX, m - x0), full = nx & ~3;
+    for (int x = 0; x < full; x += 4) {
+      const float gv = gr[x];
+      sb += gv;
 #pragma unroll
-      for (int k = 0; k < KMAX; ++k) {
-        if (k >= K) break;
-        const int xs = x + k - h;
-        if (xs >= 0 && xs < m) acc[cj * KMAX + k] = fmaf(gv, ar[xs], acc[cj * KMAX + k]);
-      }
+      for (int k = 0; k < K; ++k)
+        acc[k] = __builtin_amdgcn_mfma_f32_16x16x4f32(gv, ar[x + k], acc[k], 0, 0, 0);
+      if ((x & 28) == 28) flush();
+    }
+    if (full < nx) {  // the last positions: an operand past m may pair a zero g with a real activation
+      const bool in = full + lq < nx;
+      const float gv = gr[full];
+      sb += gv;
+#pragma unroll
+      for (int k = 0; k < K; ++k)
+        acc[k] = __builtin_amdgcn_mfma_f32_16x16x4f32(gv, in ? ar[full + k] : 0.f, acc[k], 0, 0, 0);
+    }
+    flush();
+  }
+  if (!mine) return;
+  float* pp = part + (int64_t)blockIdx.x * ((int64_t)Cout * Cin * K + Cout);
+  // D register v of lane l: output channel 4 (l / 16) + v of the wavefront's 16, input channel l % 16
+  const int c = c0 + l16;
+  if (c < Cin) {
+#pragma unroll
+    for (int v = 0; v < 4; ++v) {
+      const int o = o0 + 16 * wave + 4 * lq + v;
+      if (o >= Cout) continue;
+#pragma unroll
+      for (int k = 0; k < K; ++k)
+        pp[((int64_t)o * Cin + c) * K + k] = tot[k][v];
     }
   }
-  const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
-#pragma unroll
-  for (int j = 0; j < CG * KMAX + 1; ++j) {
-    float v = acc[j];
-#pragma unroll
-    for (int off = 32; off > 0; off >>= 1) v += __shfl_xor(v, off, 64);
-    if (lane == 0) red[wave][j] = v;
-  }
-  __syncthreads();
-  for (int j = threadIdx.x; j < CG * KMAX + 1; j += 256) {
-    const float v = ((red[0][j] + red[1][j]) + red[2][j]) + red[3][j];
-    if (j == CG * KMAX) {
-      if (blockIdx.y == 0) gb[o] = v;
-    } else {
-      const int cj = j / KMAX, k = j % KMAX;
-      if (c0 + cj < Cin && k < K) gW[((int64_t)o * Cin + c0 + cj) * K + k] = v;
-    }
+  if (blockIdx.y == 0) {
+    sb += __shfl_xor(sb, 16, 64);
+    sb += __shfl_xor(sb, 32, 64);
+    const int o = o0 + 16 * wave + l16;
+    if (lq == 0 && o < Cout) pp[(int64_t)Cout * Cin * K + o] = sb;
   }
 }
 
-// W' (Cin, Cout, K) with W'[c, o, k] = W[o, c, K - 1 - k]: the input gradient of a "same"
-// correlation is the correlation of the output gradient with W'.
-__global__ void k_flip_transpose(const float* __restrict__ W, int Cout, int Cin, int K, float* __restrict__ Wt) {
+// gW and gb from the nsplit partial sums, added in order in FP64, eight loads in flight.
+__global__ void k_wgrad_reduce(const float* __restrict__ part, int64_t nW, int64_t total, int nsplit,
+                               float* __restrict__ gW, float* __restrict__ gb) {
   const int64_t t = blockIdx.x * (int64_t)blockDim.x + threadIdx.x;
-  const int64_t n = (int64_t)Cout * Cin * K;
-  if (t >= n) return;
-  const int k = (int)(t % K);
-  const int64_t oc = t / K;
-  const int o = (int)(oc / Cin), c = (int)(oc % Cin);
-  Wt[((int64_t)c * Cout + o) * K + (K - 1 - k)] = W[t];
-}
-
-// g *= GELU'(z) elementwise.
-__global__ void k_gelu_bwd(float* __restrict__ g, const float* __restrict__ z, int64_t n) {
-  const int64_t t = blockIdx.x * (int64_t)blockDim.x + threadIdx.x;
-  if (t < n) g[t] *= gelu_grad_f(z[t]);
+  if (t >= total) return;
+  double s = 0.0;
+  int i = 0;
+  for (; i + 8 <= nsplit; i += 8) {
+    float v[8];
+#pragma unroll
+    for (int j = 0; j < 8; ++j) v[j] = part[(int64_t)(i + j) * total + t];
+#pragma unroll
+    for (int j = 0; j < 8; ++j) s += v[j];
+  }
+  for (; i < nsplit; ++i) s += part[(int64_t)i * total + t];
+  if (t < nW) gW[t] = (float)s;
+  else gb[t - nW] = (float)s;
 }
 
 // mean of B values in one block (fixed order)
@@ -337,25 +438,36 @@ __global__ void k_head_grad(const float* __restrict__ Y, int D, const float* __r
 
 static unsigned nb1(int64_t n) { return (unsigned)((n + 255) / 256); }
 
-size_t net_conv_smem(int K, int CPW) { return sizeof(float) * ((size_t)kCIC * (kTX + K - 1) + 4 * CPW * kCIC * K); }
+namespace {
+template <int K>
+hipError_t conv_go(const float* in, int Cin, const float* W, const float* bias, int Cout, int m, int64_t B,
+                   float* pre, float* act, int gelu, hipStream_t st, bool flip, const float* dz) {
+  constexpr size_t lds = sizeof(float) * ((size_t)kCIC * kWinS + 64 * conv_row(K));
+  const dim3 grid((unsigned)((m + kCX - 1) / kCX), (unsigned)((Cout + 63) / 64), (unsigned)B);
+  auto* fn = flip ? k_conv_mfma<K, true> : k_conv_mfma<K, false>;
+  if (lds > 64 * 1024) {
+    const hipError_t e = hipFuncSetAttribute((const void*)fn, hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds);
+    if (e != hipSuccess) return e;
+  }
+  hipLaunchKernelGGL(fn, grid, dim3(256), lds, st, in, Cin, W, bias, Cout, m, pre, act, gelu, dz);
+  return hipGetLastError();
+}
+}  // namespace
 
 hipError_t launch_conv_fwd(const float* in, int Cin, const float* W, const float* bias, int Cout, int K, int m,
-                           int64_t B, float* pre, float* act, int gelu, hipStream_t st) {
+                           int64_t B, float* pre, float* act, int gelu, hipStream_t st, bool flip, const float* dz) {
   if (B <= 0) return hipSuccess;
-  if (!in || !W || !act || K < 1 || K > 15 || (K % 2) == 0) return hipErrorInvalidValue;
-  const unsigned gx = (unsigned)((m + kTX - 1) / kTX);
-  if (Cout >= 16) {
-    constexpr int CPW = 4;
-    dim3 grid(gx, (unsigned)((Cout + 4 * CPW - 1) / (4 * CPW)), (unsigned)B);
-    hipLaunchKernelGGL((k_conv_fwd<CPW>), grid, dim3(256), net_conv_smem(K, CPW), st, in, Cin, W, bias, Cout, K, m,
-                       pre, act, gelu);
-  } else {
-    constexpr int CPW = 1;
-    dim3 grid(gx, (unsigned)((Cout + 3) / 4), (unsigned)B);
-    hipLaunchKernelGGL((k_conv_fwd<CPW>), grid, dim3(256), net_conv_smem(K, CPW), st, in, Cin, W, bias, Cout, K, m,
-                       pre, act, gelu);
+  if (!in || !W || !act || K < 1 || K > kMaxTaps || (K % 2) == 0) return hipErrorInvalidValue;
+  switch (K) {
+    case 1: return conv_go<1>(in, Cin, W, bias, Cout, m, B, pre, act, gelu, st, flip, dz);
+    case 3: return conv_go<3>(in, Cin, W, bias, Cout, m, B, pre, act, gelu, st, flip, dz);
+    case 5: return conv_go<5>(in, Cin, W, bias, Cout, m, B, pre, act, gelu, st, flip, dz);
+    case 7: return conv_go<7>(in, Cin, W, bias, Cout, m, B, pre, act, gelu, st, flip, dz);
+    case 9: return conv_go<9>(in, Cin, W, bias, Cout, m, B, pre, act, gelu, st, flip, dz);
+    case 11: return conv_go<11>(in, Cin, W, bias, Cout, m, B, pre, act, gelu, st, flip, dz);
+    case 13: return conv_go<13>(in, Cin, W, bias, Cout, m, B, pre, act, gelu, st, flip, dz);
+    default: return conv_go<15>(in, Cin, W, bias, Cout, m, B, pre, act, gelu, st, flip, dz);
   }
-  return hipGetLastError();
 }
 
 int bf16_cp(int Cin) { return (Cin + 7) / 8 * 8; }
@@ -389,22 +501,40 @@ hipError_t launch_conv_bf16(const void* in, bool in_f32, int Cin, const __hip_bf
   return hipGetLastError();
 }
 
+// Enough blocks (1024) for the chip; at most 64 partials, which the reduction reads in ~ 5 us, and no
+// more than there are chunks.
+int wgrad_splits(int Cin, int Cout, int m, int64_t B) {
+  const int64_t tiles = (int64_t)((Cin + 15) / 16) * ((Cout + 63) / 64);
+  const int64_t chunks = B * ((m + kGX - 1) / kGX);
+  return (int)std::max<int64_t>(1, std::min<int64_t>({chunks, 64, 1024 / tiles}));
+}
+int64_t wgrad_part_floats(int Cin, int Cout, int K, int m, int64_t B) {
+  return (int64_t)wgrad_splits(Cin, Cout, m, B) * ((int64_t)Cout * Cin * K + Cout);
+}
+
 hipError_t launch_conv_wgrad(const float* a, int Cin, const float* g, int Cout, int K, int m, int64_t B, float* gW,
-                             float* gb, hipStream_t st) {
-  if (K < 1 || K > 15) return hipErrorInvalidValue;
-  dim3 grid((unsigned)Cout, (unsigned)((Cin + 7) / 8));
-  hipLaunchKernelGGL(k_conv_wgrad, grid, dim3(256), 0, st, a, Cin, g, Cout, K, m, B, gW, gb);
-  return hipGetLastError();
-}
-
-hipError_t launch_flip_transpose(const float* W, int Cout, int Cin, int K, float* Wt, hipStream_t st) {
-  const int64_t n = (int64_t)Cout * Cin * K;
-  hipLaunchKernelGGL(k_flip_transpose, dim3(nb1(n)), dim3(256), 0, st, W, Cout, Cin, K, Wt);
-  return hipGetLastError();
-}
-
-hipError_t launch_gelu_bwd(float* g, const float* z, int64_t n, hipStream_t st) {
-  hipLaunchKernelGGL(k_gelu_bwd, dim3(nb1(n)), dim3(256), 0, st, g, z, n);
+                             float* gb, float* part, hipStream_t st) {
+  if (!part || K < 1 || K > kMaxTaps || (K % 2) == 0) return hipErrorInvalidValue;
+  const int ns = wgrad_splits(Cin, Cout, m, B);
+  const dim3 grid((unsigned)ns, (unsigned)((Cin + 15) / 16), (unsigned)((Cout + 63) / 64));
+  constexpr size_t lds = sizeof(float) * (64 * kGS + 16 * kAS);
+#define IE_WG(KK) \
+  case KK: hipLaunchKernelGGL(k_wgrad_mfma<KK>, grid, dim3(256), lds, st, a, Cin, g, Cout, m, B, part); break
+  switch (K) {
+    IE_WG(1);
+    IE_WG(3);
+    IE_WG(5);
+    IE_WG(7);
+    IE_WG(9);
+    IE_WG(11);
+    IE_WG(13);
+    IE_WG(15);
+  }
+#undef IE_WG
+  hipError_t e = hipGetLastError();
+  if (e != hipSuccess) return e;
+  const int64_t nW = (int64_t)Cout * Cin * K, total = nW + Cout;
+  hipLaunchKernelGGL(k_wgrad_reduce, dim3(nb1(total)), dim3(256), 0, st, part, nW, total, ns, gW, gb);
   return hipGetLastError();
 }
 
