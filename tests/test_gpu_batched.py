@@ -122,6 +122,34 @@ def test_batched_equals_single_instances(domain, precision, tail):
     assert st.counter(ie.CNT_STATUS) == 0
 
 
+@pytest.mark.parametrize("count", [1, 2, 256, 300])
+def test_queue_of_many_instances(count):
+    """The queue of one persistent launch takes in every instance's systems whatever their number
+    (below, at and over the 256 threads that add up the earlier instances' counts): copies of three
+    problems give the same bits wherever they stand in the batch, and agree with the oracle."""
+    kinds = [syn.gaussian_problem(n, N, 5.0, 8.0, 2, 0.25, 3, 100.0, 300 + n, name="q%d" % n)
+             for n, N in ((64, 4), (48, 3), (96, 5))]
+    Ps = [ie.Problem.from_synthetic(kinds[j % 3]) for j in range(count)]
+    lats = [P.lattice() for P in Ps]
+    nodes = [ie.quadrature_elliptic(3, 100.0)] * count
+    say("queue of", count)
+    runner = ie.BatchedRunner(Ps, nodes, make_opts("lattice", ie.FP64, tail_systems=100000),
+                              ys=[kinds[j % 3].y for j in range(count)], lattices=lats)
+    code = runner.run()
+    torch.cuda.synchronize()
+    assert code == ie.OK
+    assert count < 2 or runner.one_launch()
+    assert runner.stats(code).converged.all()
+    Xs, mus = runner.results()
+    for j in range(count):
+        assert torch.equal(Xs[j], Xs[j % 3]) and torch.equal(mus[j], mus[j % 3]), j
+    for j in range(min(3, count)):
+        pr = kinds[j]
+        s0, p0, _ = ref.quadrature_elliptic(pr.Q, pr.ell)
+        want = np.sqrt(pr.N - 1) * ref.perturbation_update_quadrature(ref.DenseProblem.from_problem(pr), s0, p0)
+        assert upd(Xs[j].cpu().numpy(), want) < 1e-6, pr.name
+
+
 def test_batched_instance_matches_oracle():
     probs = batch()
     Ps = [ie.Problem.from_synthetic(pr) for pr in probs]
