@@ -415,11 +415,11 @@ __global__ __launch_bounds__(NT) void k_pcg_tail(TailInst one, const TailInst* _
   // loads of the packed FP32 band.  Short chunks measured fastest at the n = 4096 lattice (the
   // FP64 kernel 0.56 ms per launch with 8 entries against 0.67 ms with 16; FP32 0.45 ms with 8
   // against 0.57 ms with 32)
-  // With four rows a thread, 2 FP64 entries (4 entries of the packed FP32 band) a chunk still keep
-  // four 16-byte loads in flight per thread, and the registers they save keep the kernel that serves
-  // many instances from spilling.
-  constexpr int CH = RPT >= 4 ? 2 : 8;
-  constexpr int CHQ = RPT >= 4 ? 4 : 8;
+  // With four rows a thread, 4 FP64 entries (8 of the packed FP32 band) a chunk keep eight 16-byte
+  // loads in flight per thread; the 512-thread kernels up to P = 12 have the registers for them (at 2
+  // and 4 entries k_pcg_tail<4, 4, 512, float> over many instances took 25.0 ms for 22.3).
+  constexpr int CH = RPT >= 4 ? 4 : 8;
+  constexpr int CHQ = 8;
   // the Ritz vectors of the thread's rows stay in registers when they fit
   constexpr bool kCache = tail_caches_ritz(P, RPT, NT);
   constexpr bool kLdsSums = tail_lds_sums(2 * P + 1, NT, RPT);
@@ -546,11 +546,16 @@ __global__ __launch_bounds__(NT) void k_pcg_tail(TailInst one, const TailInst* _
     if (!resumed) {
       if (tid == 0) s_idx = atomicAdd(qctr, 1);
       __syncthreads();
-      const int idx = s_idx;
+      const int idx = __builtin_amdgcn_readfirstlane(s_idx);
       __syncthreads();  // every thread has read s_idx before it is written again
       if (idx >= na) break;
       e = act[idx];
     }
+    // the entry is the same in every lane; said so, the descriptor's fields are scalar loads and the band's
+    // buffer descriptor stays in scalar registers.  From a per-lane entry every load of the band became a
+    // loop over the descriptors found in the wavefront, and a batch's iteration took three times a single
+    // instance's (k_pcg_tail<4, 4, 512, float> on 20 instances of 1024 < m <= 2048: 33.8 ms, now 22.3).
+    e = __builtin_amdgcn_readfirstlane(e);
     const int j = MULTI ? (int)(e >> kTailSysBits) : 0;
     const int32_t s = MULTI ? (e & ((1 << kTailSysBits) - 1)) : e;
     const TailInst& d = MULTI ? table[j] : one;
@@ -558,9 +563,9 @@ __global__ __launch_bounds__(NT) void k_pcg_tail(TailInst one, const TailInst* _
     const TailCheck& chk = d.chk;
     const bool check = d.r0 != nullptr && chk.b != nullptr;
     if (!resumed) {
-      if (st.done[s] != 0) continue;
+      if (__builtin_amdgcn_readfirstlane(st.done[s]) != 0) continue;
       // a system whose sweep budget is spent stays live for the host to finish
-      if (check && chk.max_sweeps > 0 && chk.sweeps[s] >= chk.max_sweeps) continue;
+      if (check && chk.max_sweeps > 0 && __builtin_amdgcn_readfirstlane(chk.sweeps[s]) >= chk.max_sweeps) continue;
     }
     if (MULTI && j != cur) {
       cur = j;
@@ -941,8 +946,10 @@ __global__ __launch_bounds__(NT) void k_pcg_tail(TailInst one, const TailInst* _
     const int nsw = check ? (resumed ? rs_nsw : chk.sweeps[s]) + 1 : 0;
     // the next sweep runs here only after a converged inner solve (breakdowns and the iteration
     // cap go to the status below)
-    const bool again = check && state == 1 && isfinite(rr) && !(rr <= chk.rtol) && it < st.max_iter && !chk.fixed &&
-                       chk.max_sweeps > 0 && nsw < chk.max_sweeps;
+    // (the same in every lane; said so, or the next system's entry would count as the lane's own)
+    const bool again = __builtin_amdgcn_readfirstlane(
+        check && state == 1 && isfinite(rr) && !(rr <= chk.rtol) && it < st.max_iter && !chk.fixed &&
+        chk.max_sweeps > 0 && nsw < chk.max_sweeps);
     if (tid == 0) {
       if (st.prof.vectors) {
         const int done_its = it - it0;
