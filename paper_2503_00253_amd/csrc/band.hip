@@ -14,6 +14,7 @@
 // wavefront read consecutive rows of one plane).  Entries whose neighbour falls off a
 // non-periodic grid are 0.
 #include <atomic>
+#include <type_traits>
 
 #include "internal.hpp"
 
@@ -243,6 +244,238 @@ hipError_t band_apply_typed(const Grid& g, const T* band, int64_t ldb, const T* 
   return hipGetLastError();
 }
 
+// The FP64 product on MFMA.  A wavefront takes 16 consecutive rows and 16 systems; the contraction
+// runs over the rows' window k = d + i (i the row within the 16, d the stencil offset), so the A
+// fragments are the band skewed by the row and the B fragments the V window, and each output is the
+// chain of fused multiply-adds over ascending d that k_band_apply forms: v_mfma_f64_16x16x4f64 adds
+// its four products one after the other, and the window's corners outside the band enter as zeros,
+// which change no sum of finite terms.  A window with an infinity or NaN takes the plain loop
+// below, where those reach only the rows that couple to them.
+//
+// k_band_apply reads one LDS window entry per multiply-add and lane and is bound by that (4096
+// points, w = 319, 640 systems: 125 us, 13 TFLOP/s); here two 512-byte fragments feed 1024 of them:
+// 59 us, half of it the matrix cores' own time, the rest the staging of the windows, which two
+// blocks a CU overlap in part.  (32 systems a wavefront read the band half as often, but leave one
+// block a CU: 63 us.)
+// The planes of 16 offsets are loaded row-contiguous (128 bytes each), kPre chunks ahead, and pass
+// through a wavefront's own ring of 32 window positions x 16 rows in LDS, written at [d + i][i] and
+// read a fragment at a time, both without bank conflicts; the ring needs no block barrier.  The V
+// window's pitch is 2 mod 32 doubles, so the 16 systems x 2 positions of a half wavefront's read
+// fall into different banks.
+constexpr int kMfWaves = 4;
+constexpr int kMfPre = 4;    // chunks of planes in flight
+constexpr int kMfStage = 6;  // window positions a lane has in flight while staging
+constexpr int kMfMaxLds = 150 * 1024;
+
+__host__ __device__ inline int mf_chunks(int bx) { return (2 * bx + 16 + 15) / 16; }
+__host__ __device__ inline int mf_window(int bx) { return 16 * (kMfWaves - 1 + mf_chunks(bx)); }
+__host__ __device__ inline int mf_pitch(int bx) { return (mf_window(bx) + 29) / 32 * 32 + 2; }
+inline size_t mf_lds(int bx) {
+  return sizeof(double) * ((size_t)16 * mf_pitch(bx) + (size_t)kMfWaves * 32 * 16);
+}
+
+__device__ inline double mf_load(__amdgpu_buffer_rsrc_t rs, uint32_t off) {
+  return __builtin_bit_cast(double, __builtin_amdgcn_raw_buffer_load_b64(rs, off, 0, 0));
+}
+// LDS of one wavefront: its accesses complete in order, so only the compiler has to keep them so
+__device__ inline void mf_wave_sync() {
+  __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
+  __builtin_amdgcn_wave_barrier();
+  __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
+}
+
+__global__ __launch_bounds__(64 * kMfWaves) void k_band_apply_mfma(
+    Grid g, const double* __restrict__ band, int64_t ldb, const double* __restrict__ V, int64_t ldv, int64_t vcols,
+    int B, const int32_t* __restrict__ Bdev, double* __restrict__ Tout, int64_t ldt, int tiles_per_layer, ProfDev prof,
+    int32_t* __restrict__ zero_counter) {
+  constexpr int TX = 16 * kMfWaves;
+  constexpr int NC = 16;
+  constexpr int PER = NC / kMfWaves;
+  if (Bdev) B = *Bdev;
+  if (blockIdx.x == 0 && blockIdx.y == 0 && threadIdx.x == 0) {
+    if (zero_counter) {  // list and live counters of the next PCG step (nobody reads them now)
+      zero_counter[0] = 0;
+      zero_counter[1] = 0;
+    }
+    if (prof.vectors) {
+      atomicAdd(prof.vectors, (unsigned long long)B);
+      atomicAdd(prof.flops, (double)B * prof.flops_per_vector);
+      atomicAdd(prof.bytes, (double)B * prof.bytes_per_vector);
+    }
+  }
+  const int b0 = blockIdx.y * NC;
+  if (b0 >= B) return;
+  extern __shared__ __attribute__((aligned(16))) unsigned char smem_raw[];
+  const int nx = g.nx, nz = g.nz, bx = g.bx, bz = g.bz;
+  const int w = 2 * bx + 1;
+  const int nch = mf_chunks(bx), WX = mf_window(bx), WP = mf_pitch(bx);
+  const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+  double* Vw = reinterpret_cast<double*>(smem_raw);  // NC x WP
+  double* ring = Vw + NC * WP + wave * (32 * 16);    // [32 window positions][16 rows]
+  // workgroups go to the eight XCDs in turn: each XCD takes a run of neighbouring tiles, whose
+  // windows overlap in its L2
+  const int nt = gridDim.x, xcd = blockIdx.x & 7, per = nt >> 3, rem = nt & 7;
+  const int tile = xcd * per + min(xcd, rem) + (blockIdx.x >> 3);
+  const int z = tile / tiles_per_layer;
+  const int x0 = (tile % tiles_per_layer) * TX;
+  // A lane l -> (row l%16, k l/16); B lane l -> (k l/16, system l%16); D register v of lane l ->
+  // (row 4v + l/16, system l%16)
+  const int i = lane & 15, kq = lane >> 4;
+  const int xr = x0 + 16 * wave;
+  const int ncol = (int)min((int64_t)B, vcols) - b0;  // systems the block has
+  // the slot of (offset 4u + kq, row i) in the ring for an even chunk; an odd chunk's is 16 positions on
+  int slot[4];
+#pragma unroll
+  for (int u = 0; u < 4; ++u) slot[u] = (4 * u + kq + i) * 16 + i;
+  const uint32_t chunk = (uint32_t)(16 * ldb * (int64_t)sizeof(double));  // bytes of a chunk's planes
+  const bool one_wrap = nx >= TX + bx;
+
+  band_d4 acc = {0.0, 0.0, 0.0, 0.0};
+
+  for (int li = 0; li < 2 * bz + 1; ++li) {
+    int zz = z + li - bz;
+    if (g.pz) zz = wrap_idx(zz, nz);
+    else if (zz < 0 || zz >= nz) continue;  // uniform over the block
+    __syncthreads();
+    // this stencil row's planes: offsets past the band and rows past the layer lie outside the
+    // buffer and read as zeros
+    const __amdgpu_buffer_rsrc_t rs = __builtin_amdgcn_make_buffer_rsrc(
+        const_cast<double*>(band + (int64_t)(li * w) * ldb), (short)0, (int)(w * ldb * (int64_t)sizeof(double)),
+        0x00020000);
+    uint32_t off[4];
+#pragma unroll
+    for (int u = 0; u < 4; ++u)
+      off[u] = xr + i < nx ? (uint32_t)(((int64_t)(4 * u + kq) * ldb + (int64_t)z * nx + xr + i) * sizeof(double))
+                           : 0x80000000u;
+    // the first chunks' planes are under way while the window is staged
+    double pre[kMfPre][4];
+#pragma unroll
+    for (int c = 0; c < kMfPre; ++c)
+#pragma unroll
+      for (int u = 0; u < 4; ++u) {
+        pre[c][u] = mf_load(rs, off[u]);
+        off[u] += chunk;
+      }
+    // each wave stages the window of its PER systems: a column's buffer is the layer's row, so
+    // neighbours off a grid that is not periodic read as zeros, and so do systems past the last
+    double fin = 0.0;  // a NaN once any staged value is not finite
+    for (int t0 = lane; t0 < WX; t0 += 64 * kMfStage) {
+      double v[kMfStage][PER];
+#pragma unroll
+      for (int s = 0; s < kMfStage; ++s) {
+        const int t = t0 + 64 * s;
+        int kx = x0 - bx + t;
+        if (g.px) {
+          if (one_wrap) kx = kx < 0 ? kx + nx : (kx >= nx ? kx - nx : kx);
+          else kx = wrap_idx(kx, nx);
+        }
+        const uint32_t o = t < TX + 2 * bx ? (uint32_t)kx * 8u : 0x80000000u;
+#pragma unroll
+        for (int k = 0; k < PER; ++k) {
+          const int c = wave + kMfWaves * k;
+          const __amdgpu_buffer_rsrc_t rv = __builtin_amdgcn_make_buffer_rsrc(
+              const_cast<double*>(V + (int64_t)(b0 + (c < ncol ? c : 0)) * ldv + (int64_t)zz * nx), (short)0,
+              c < ncol ? nx * 8 : 0, 0x00020000);
+          v[s][k] = mf_load(rv, o);
+        }
+      }
+#pragma unroll
+      for (int s = 0; s < kMfStage; ++s)
+#pragma unroll
+        for (int k = 0; k < PER; ++k) {
+          fin = fma(v[s][k], 0.0, fin);
+          if (t0 + 64 * s < WX) Vw[(wave + kMfWaves * k) * WP + t0 + 64 * s] = v[s][k];
+        }
+    }
+    // window positions below the first row's own offset lie outside the band
+#pragma unroll
+    for (int u = 0; u < 4; ++u) ring[64 * u + lane] = 0.0;
+    if (__syncthreads_or(fin != 0.0)) {
+      for (int v = 0; v < 4; ++v) {
+        const int row = 4 * v + kq;
+        if (xr + row >= nx) continue;
+        const double* bp = band + (int64_t)(li * w) * ldb + (int64_t)z * nx + xr + row;
+        for (int d = 0; d < w; ++d) acc[v] = fma(bp[(int64_t)d * ldb], Vw[i * WP + 16 * wave + row + d], acc[v]);
+      }
+      continue;
+    }
+    // chunk c's planes go into the ring and its fragments into registers while the matrix core
+    // works on chunk c - 1
+    const double* vw = Vw + i * WP + 16 * wave + kq;
+    double a[2][4], b[2][4];
+#pragma unroll
+    for (int u = 0; u < 4; ++u) a[1][u] = b[1][u] = 0.0;
+    auto step = [&](int c, auto parity, double (&pc)[4], bool more) {
+      constexpr int h = parity.value;
+#pragma unroll
+      for (int u = 0; u < 4; ++u) ring[slot[u] ^ (256 * h)] = pc[u];
+      if (more) {
+#pragma unroll
+        for (int u = 0; u < 4; ++u) {
+          pc[u] = mf_load(rs, off[u]);
+          off[u] += chunk;
+        }
+      }
+      mf_wave_sync();
+#pragma unroll
+      for (int u = 0; u < 4; ++u) {
+        a[h][u] = ring[256 * h + 64 * u + lane];
+        b[h][u] = vw[16 * c + 4 * u];
+      }
+      mf_wave_sync();
+      __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+      for (int u = 0; u < 4; ++u)
+        acc = __builtin_amdgcn_mfma_f64_16x16x4f64(a[1 - h][u], b[1 - h][u], acc, 0, 0, 0);
+      __builtin_amdgcn_sched_barrier(0);
+    };
+    using even = std::integral_constant<int, 0>;
+    using uneven = std::integral_constant<int, 1>;
+    // whole groups without a branch between their loads and waits, then the rest
+    int c = 0;
+    for (; c + kMfPre <= nch; c += kMfPre) {
+      step(c, even{}, pre[0], true);
+      step(c + 1, uneven{}, pre[1], true);
+      step(c + 2, even{}, pre[2], true);
+      step(c + 3, uneven{}, pre[3], true);
+    }
+    if (c < nch) step(c, even{}, pre[0], false);
+    if (c + 1 < nch) step(c + 1, uneven{}, pre[1], false);
+    if (c + 2 < nch) step(c + 2, even{}, pre[2], false);
+    // the last chunk
+    const bool odd = (nch - 1) & 1;
+#pragma unroll
+    for (int u = 0; u < 4; ++u)
+      acc = __builtin_amdgcn_mfma_f64_16x16x4f64(odd ? a[1][u] : a[0][u], odd ? b[1][u] : b[0][u], acc, 0, 0, 0);
+  }
+  if (b0 + i < B) {
+#pragma unroll
+    for (int v = 0; v < 4; ++v) {
+      const int row = 4 * v + kq;
+      if (xr + row < nx) Tout[(int64_t)(b0 + i) * ldt + (int64_t)z * nx + xr + row] = acc[v];
+    }
+  }
+}
+
+hipError_t band_apply_mfma(const Grid& g, const double* band, int64_t ldb, const double* V, int64_t ldv, int64_t vcols,
+                           int64_t B, const int32_t* Bdev, double* Tout, int64_t ldt, hipStream_t st,
+                           const ProfDev& pf, int32_t* zc) {
+  constexpr int TX = 16 * kMfWaves;
+  const int tiles_per_layer = (g.nx + TX - 1) / TX;
+  const size_t smem = mf_lds(g.bx);
+  static std::atomic<bool> attr{false};  // concurrent first calls set the same attribute twice: harmless
+  if (smem > 64 * 1024 && !attr.load(std::memory_order_acquire)) {
+    const hipError_t e = hipFuncSetAttribute(reinterpret_cast<const void*>(&k_band_apply_mfma),
+                                             hipFuncAttributeMaxDynamicSharedMemorySize, kMfMaxLds);
+    if (e != hipSuccess) return e;
+    attr.store(true, std::memory_order_release);
+  }
+  dim3 grid((unsigned)(tiles_per_layer * g.nz), (unsigned)((B + 15) / 16));
+  hipLaunchKernelGGL((k_band_apply_mfma), grid, dim3(64 * kMfWaves), smem, st, g, band, ldb, V, ldv, vcols, (int)B,
+                     Bdev, Tout, ldt, tiles_per_layer, pf, zc);
+  return hipGetLastError();
+}
+
 }  // namespace
 
 static int band_systems_per_block(const Grid& g, size_t elem, int64_t B) {
@@ -258,6 +491,19 @@ static int band_systems_per_block(const Grid& g, size_t elem, int64_t B) {
     if ((size_t)nsb * (64 + 2 * g.bx) * elem <= 48 * 1024 && (nsb <= 16 || B > nsb / 2)) return nsb;
   }
   return 8;
+}
+
+// Where the FP64 product runs on the matrix cores.  The window of 16 rows is w + 15 positions, in
+// chunks of 16, so a narrow band leaves them idle work: at w = 79 they are as fast as k_band_apply
+// for 640 systems of 4096 points (71 us a call of the covariance apply against 75) and faster below,
+// at w = 39 slower (67 against 62); k_band_apply needs many systems to fill the chip, and up to 64
+// systems the matrix cores win at any width but the narrowest (16 x 256 points, 7 x 21 stencil, 40
+// systems: 58 us against 77; w = 7: the same).  The window has to fit in LDS (bx < 480) and a
+// stencil row's planes within a buffer's 32-bit offsets.
+bool band_apply_on_mfma(const Grid& g, int64_t ldb, int64_t B) {
+  const int w = 2 * g.bx + 1;
+  return (w >= 64 || (w >= 16 && B <= 64)) && mf_lds(g.bx) <= (size_t)kMfMaxLds && g.nx < (1 << 28) &&
+         (w + 16 * (kMfPre + 2)) * ldb * (int64_t)sizeof(double) < (int64_t(1) << 31);
 }
 
 hipError_t launch_band_build(Prec prec, const Grid& g, const double* Z, int64_t ldz, int64_t N, void* band,
@@ -296,6 +542,7 @@ hipError_t launch_band_apply(Prec prec, const Grid& g, const void* band, int64_t
     const double* b = (const double*)band;
     const double* v = (const double*)V;
     double* t = (double*)T;
+    if (band_apply_on_mfma(g, ldb, B)) return band_apply_mfma(g, b, ldb, v, ldv, vcols, B, Bdev, t, ldt, st, pf, zc);
     switch (band_systems_per_block(g, sizeof(double), B)) {
       case 64: return band_apply_typed<double, 64>(g, b, ldb, v, ldv, vcols, B, Bdev, t, ldt, st, pf, zc);
       case 32: return band_apply_typed<double, 32>(g, b, ldb, v, ldv, vcols, B, Bdev, t, ldt, st, pf, zc);
