@@ -29,41 +29,47 @@ __global__ void k_unit_cols(int64_t rows, int64_t j0, int64_t bc, double* __rest
 }
 
 // V[:, c] = H^T R^{-1/2} e_{j0 + c}: row j0 + c of H, scaled by r^{-1/2}, on a zeroed state
-// column.  One thread per column adds the row's entries in order (repeated indices sum).
-__global__ void k_scatter_unit_obs(const int32_t* __restrict__ h_ptr, const int32_t* __restrict__ h_idx,
-                                   const double* __restrict__ h_w, const double* __restrict__ r_var, int64_t n,
-                                   int64_t j0, int64_t bc, double* __restrict__ V, int64_t ldv) {
-  const int64_t c = blockIdx.x * (int64_t)blockDim.x + threadIdx.x;
+// column.  One wavefront per column (a thread per column took 61 us for rows of 177 entries, now
+// TBD); repeated indices, which the input checks flag, sum in any order.
+__global__ __launch_bounds__(256) void k_scatter_unit_obs(const int32_t* __restrict__ h_ptr,
+                                                          const int32_t* __restrict__ h_idx,
+                                                          const double* __restrict__ h_w,
+                                                          const double* __restrict__ r_var, int64_t n, int64_t j0,
+                                                          int64_t bc, double* __restrict__ V, int64_t ldv) {
+  const int64_t c = blockIdx.x * (int64_t)4 + (threadIdx.x >> 6);
   if (c >= bc) return;
   const int64_t k = j0 + c;
   const double sc = 1.0 / sqrt(r_var[k]);
   double* col = V + c * ldv;
-  for (int32_t e = h_ptr[k]; e < h_ptr[k + 1]; ++e) {
+  for (int32_t e = h_ptr[k] + (int32_t)(threadIdx.x & 63); e < h_ptr[k + 1]; e += 64) {
     const int32_t j = h_idx[e];
-    if (j >= 0 && j < n) col[j] += sc * h_w[e];
+    if (j >= 0 && j < n) atomicAdd(&col[j], sc * h_w[e]);
   }
 }
 
 // S[(j0 + c) * lds + r] = (S e_{j0+c})_r from the apply output T: the observation-domain
-// output itself, or R^{-1/2} H T for a state-domain output.
+// output itself, or R^{-1/2} H T for a state-domain output.  WAVE: a wavefront per entry
+// (kWaveOutputs).
+template <bool WAVE>
 __global__ void k_gather_s_cols(int obs_domain, const double* __restrict__ T, int64_t ldt,
                                 const int32_t* __restrict__ h_ptr, const int32_t* __restrict__ h_idx,
                                 const double* __restrict__ h_w, const double* __restrict__ r_var, int64_t n,
                                 int64_t m, int64_t j0, int64_t bc, double* __restrict__ S, int64_t lds) {
-  const int64_t t = blockIdx.x * (int64_t)blockDim.x + threadIdx.x;
+  int64_t t = blockIdx.x * (int64_t)blockDim.x + threadIdx.x;
+  if (WAVE) t /= 64;
   if (t >= m * bc) return;
   const int64_t c = t / m, r = t - c * m;
   const double* col = T + c * ldt;
+  if (WAVE) {  // the state domain
+    const double w = row_dot_wave(h_idx, h_w, h_ptr[r], h_ptr[r + 1], n, col) / sqrt(r_var[r]);
+    if ((threadIdx.x & 63) == 63) S[(j0 + c) * lds + r] = w;
+    return;
+  }
   double v;
   if (obs_domain) {
     v = col[r];
   } else {
-    double a = 0.0;
-    for (int32_t e = h_ptr[r]; e < h_ptr[r + 1]; ++e) {
-      const int32_t j = h_idx[e];
-      if (j >= 0 && j < n) a += h_w[e] * col[j];
-    }
-    v = a / sqrt(r_var[r]);
+    v = row_dot(h_idx, h_w, h_ptr[r], h_ptr[r + 1], n, col) / sqrt(r_var[r]);
   }
   S[(j0 + c) * lds + r] = v;
 }
@@ -151,7 +157,7 @@ hipError_t launch_scatter_unit_obs(const int32_t* h_ptr, const int32_t* h_idx, c
                                    const double* r_var, int64_t n, int64_t j0, int64_t bc, double* V, int64_t ldv,
                                    hipStream_t st) {
   if (bc <= 0) return hipSuccess;
-  hipLaunchKernelGGL(k_scatter_unit_obs, dim3(nblocks(bc)), dim3(256), 0, st, h_ptr, h_idx, h_w, r_var, n, j0, bc,
+  hipLaunchKernelGGL(k_scatter_unit_obs, dim3((unsigned)((bc + 3) / 4)), dim3(256), 0, st, h_ptr, h_idx, h_w, r_var, n, j0, bc,
                      V, ldv);
   return hipGetLastError();
 }
@@ -160,8 +166,12 @@ hipError_t launch_gather_s_cols(int obs_domain, const double* T, int64_t ldt, co
                                 const int32_t* h_idx, const double* h_w, const double* r_var, int64_t n, int64_t m,
                                 int64_t j0, int64_t bc, double* S, int64_t lds, hipStream_t st) {
   if (m <= 0 || bc <= 0) return hipSuccess;
-  hipLaunchKernelGGL(k_gather_s_cols, dim3(nblocks(m * bc)), dim3(256), 0, st, obs_domain, T, ldt, h_ptr, h_idx,
-                     h_w, r_var, n, m, j0, bc, S, lds);
+  if (!obs_domain && m * bc <= kWaveOutputs)
+    hipLaunchKernelGGL(k_gather_s_cols<true>, dim3(nblocks(64 * m * bc)), dim3(256), 0, st, obs_domain, T, ldt, h_ptr,
+                       h_idx, h_w, r_var, n, m, j0, bc, S, lds);
+  else
+    hipLaunchKernelGGL(k_gather_s_cols<false>, dim3(nblocks(m * bc)), dim3(256), 0, st, obs_domain, T, ldt, h_ptr,
+                       h_idx, h_w, r_var, n, m, j0, bc, S, lds);
   return hipGetLastError();
 }
 

@@ -49,25 +49,26 @@ __global__ void k_ens_stats(const double* __restrict__ X, int64_t n, int64_t N, 
   }
 }
 
-// Column counts of H (one thread per CSR row); also validates indices and that the entry count
-// fits the cap entries the CSC copy has room for.
+// Column counts of H; also validates indices and that the entry count fits the cap entries the CSC
+// copy has room for.  kRowLanes lanes share a CSR row: a thread for a whole row waited out an atomic
+// per entry (100 rows of 177 entries: 79 us, now TBD).
+constexpr int kRowLanes = 16;
 __global__ void k_csc_count(const int32_t* __restrict__ h_ptr, const int32_t* __restrict__ h_idx, int64_t m,
                             int64_t n, int64_t cap, int32_t* __restrict__ cnt, int32_t* __restrict__ flags) {
-  int64_t r = blockIdx.x * (int64_t)blockDim.x + threadIdx.x;
+  const int64_t t = blockIdx.x * (int64_t)blockDim.x + threadIdx.x;
+  const int64_t r = t / kRowLanes;
   if (r >= m) return;
   const int32_t e0 = h_ptr[r], e1 = h_ptr[r + 1];
   if (e1 < e0 || e0 < 0 || e1 > h_ptr[m] || (int64_t)h_ptr[m] > cap || (r == 0 && e0 != 0)) {
     atomicOr(flags, kFlagBadInput);
     return;
   }
-  int32_t prev = -1;
-  for (int32_t e = e0; e < e1; ++e) {
+  for (int32_t e = e0 + (int32_t)(t % kRowLanes); e < e1; e += kRowLanes) {
     const int32_t c = h_idx[e];
-    if (c < 0 || c >= n || c <= prev) {
+    if (c < 0 || c >= n || (e > e0 && c <= h_idx[e - 1])) {
       atomicOr(flags, kFlagBadInput);
       return;
     }
-    prev = c;
     atomicAdd(&cnt[c], 1);
   }
 }
@@ -103,9 +104,11 @@ __global__ void k_csc_fill(const int32_t* __restrict__ h_ptr, const int32_t* __r
                            const double* __restrict__ h_w, int64_t m, const int32_t* __restrict__ col_ptr,
                            int32_t* __restrict__ cursor, int32_t* __restrict__ row_of, double* __restrict__ w_of,
                            const int32_t* __restrict__ flags) {
-  int64_t r = blockIdx.x * (int64_t)blockDim.x + threadIdx.x;
+  const int64_t t = blockIdx.x * (int64_t)blockDim.x + threadIdx.x;
+  const int64_t r = t / kRowLanes;
   if (r >= m || *flags) return;
-  for (int32_t e = h_ptr[r]; e < h_ptr[r + 1]; ++e) {
+  const int32_t e1 = h_ptr[r + 1];
+  for (int32_t e = h_ptr[r] + (int32_t)(t % kRowLanes); e < e1; e += kRowLanes) {
     const int32_t c = h_idx[e];
     const int32_t pos = col_ptr[c] + atomicAdd(&cursor[c], 1);
     row_of[pos] = (int32_t)r;
@@ -113,12 +116,37 @@ __global__ void k_csc_fill(const int32_t* __restrict__ h_ptr, const int32_t* __r
   }
 }
 
-// Sort each column's entries by row so the scatter sums in a fixed order.
+// Sort each column's entries by row so the scatter sums in a fixed order.  Up to kSortRegs entries
+// are loaded at once and written where their rank among them puts them (a column's rows differ); the
+// insertion sort of longer columns waits for memory at every step.
+constexpr int kSortRegs = 16;
 __global__ void k_csc_sort(const int32_t* __restrict__ col_ptr, int64_t n, int32_t* __restrict__ row_of,
                            double* __restrict__ w_of, const int32_t* __restrict__ flags) {
   int64_t c = blockIdx.x * (int64_t)blockDim.x + threadIdx.x;
   if (c >= n || *flags) return;
   const int32_t a = col_ptr[c], b = col_ptr[c + 1];
+  if (b - a < 2) return;
+  if (b - a <= kSortRegs) {
+    int32_t rk[kSortRegs];
+    double wk[kSortRegs];
+#pragma unroll
+    for (int i = 0; i < kSortRegs; ++i) {
+      const int32_t e = min(a + i, b - 1);
+      rk[i] = a + i < b ? row_of[e] : INT32_MAX;
+      wk[i] = w_of[e];
+    }
+#pragma unroll
+    for (int i = 0; i < kSortRegs; ++i) {
+      int32_t pos = a;
+#pragma unroll
+      for (int j = 0; j < kSortRegs; ++j) pos += rk[j] < rk[i];
+      if (a + i < b) {
+        row_of[pos] = rk[i];
+        w_of[pos] = wk[i];
+      }
+    }
+    return;
+  }
   for (int32_t i = a + 1; i < b; ++i) {
     const int32_t rk = row_of[i];
     const double wk = w_of[i];
@@ -137,12 +165,7 @@ __global__ void k_csc_sort(const int32_t* __restrict__ col_ptr, int64_t n, int32
 __device__ inline double obs_rhs_entry(const int32_t* __restrict__ h_ptr, const int32_t* __restrict__ h_idx,
                                        const double* __restrict__ h_w, const double* __restrict__ r_var,
                                        const double* __restrict__ Z, int64_t n, int64_t r, int64_t i) {
-  double acc = 0.0;
-  for (int32_t e = h_ptr[r]; e < h_ptr[r + 1]; ++e) {
-    const int32_t j = h_idx[e];
-    if (j >= 0 && j < n) acc += h_w[e] * Z[j + i * n];  // invalid indices are flagged elsewhere
-  }
-  return acc / sqrt(r_var[r]);
+  return row_dot(h_idx, h_w, h_ptr[r], h_ptr[r + 1], n, Z + i * n) / sqrt(r_var[r]);
 }
 
 // rhs[s * ld + r] = dinv_r * sum_e w_e Z[idx_e, i], i = (s - s0) % N
@@ -157,29 +180,38 @@ __global__ void k_obs_rhs(const int32_t* __restrict__ h_ptr, const int32_t* __re
 }
 
 // The same for systems 0 .. cnt-1 over the whole ld x spad block: zeros in the padding rows
-// (r >= m) and padding systems (s >= cnt).
+// (r >= m) and padding systems (s >= cnt).  WAVE: a wavefront per entry (kWaveOutputs).
+template <bool WAVE>
 __global__ void k_obs_rhs_padded(const int32_t* __restrict__ h_ptr, const int32_t* __restrict__ h_idx,
                                  const double* __restrict__ h_w, const double* __restrict__ r_var,
                                  const double* __restrict__ Z, int64_t n, int64_t N, int64_t m,
                                  double* __restrict__ rhs, int64_t ld, int64_t cnt, int64_t spad) {
-  const int64_t t = blockIdx.x * (int64_t)blockDim.x + threadIdx.x;
+  int64_t t = blockIdx.x * (int64_t)blockDim.x + threadIdx.x;
+  if (WAVE) t /= 64;
   if (t >= ld * spad) return;
   const int64_t c = t / ld, r = t % ld;
+  if (WAVE) {
+    double v = 0.0;
+    if (c < cnt && r < m)
+      v = row_dot_wave(h_idx, h_w, h_ptr[r], h_ptr[r + 1], n, Z + (c % N) * n) / sqrt(r_var[r]);
+    if ((threadIdx.x & 63) == 63) rhs[t] = v;
+    return;
+  }
   rhs[t] = (c < cnt && r < m) ? obs_rhs_entry(h_ptr, h_idx, h_w, r_var, Z, n, r, c % N) : 0.0;
 }
 
+// R^{-1/2} (y - H mu), WAVE as above
+template <bool WAVE>
 __global__ void k_innovation(const int32_t* __restrict__ h_ptr, const int32_t* __restrict__ h_idx,
                              const double* __restrict__ h_w, const double* __restrict__ r_var,
                              const double* __restrict__ y, const double* __restrict__ mu, int64_t m, int64_t n,
                              double* __restrict__ out, int64_t ld, int64_t s) {
-  const int64_t r = blockIdx.x * (int64_t)blockDim.x + threadIdx.x;
+  int64_t r = blockIdx.x * (int64_t)blockDim.x + threadIdx.x;
+  if (WAVE) r /= 64;
   if (r >= m) return;
-  double hm = 0.0;
-  for (int32_t e = h_ptr[r]; e < h_ptr[r + 1]; ++e) {
-    const int32_t j = h_idx[e];
-    if (j >= 0 && j < n) hm += h_w[e] * mu[j];
-  }
-  out[s * ld + r] = (y[r] - hm) / sqrt(r_var[r]);
+  const double hm = WAVE ? row_dot_wave(h_idx, h_w, h_ptr[r], h_ptr[r + 1], n, mu)
+                         : row_dot(h_idx, h_w, h_ptr[r], h_ptr[r + 1], n, mu);
+  if (!WAVE || (threadIdx.x & 63) == 63) out[s * ld + r] = (y[r] - hm) / sqrt(r_var[r]);
 }
 
 __device__ inline int32_t wrap_offset(int32_t d, int32_t len, int32_t periodic) {
@@ -204,8 +236,26 @@ __device__ inline double stencil_value(const Grid& g, int64_t a, int64_t b) {
 // of members at a time (member-major, so a wave's pairs with consecutive f read consecutive
 // words).  Rows longer than the staging buffer read Z from global memory.  Entry indices
 // outside [0, n) are skipped (the CSC build flags them).
+// Rows of up to kDiagRow entries also keep their grid points and weights in LDS, with the pair (e, f)
+// and the stencil offset formed by additions: per pair, five 64-bit divisions and six loads from
+// memory took most of the time.  From kDiagTile entries on, tiles of 16 x 16 pairs have their
+// members' dot products formed by the matrix cores (the plain loop is bound by its two LDS reads a
+// multiply-add) and are weighted and summed where they stand.  (100 rows of 177 entries, 20
+// members: 200 us, now TBD.)
 constexpr int kDiagThreads = 256;
 constexpr int kDiagStage = 4096;  // doubles
+constexpr int kDiagRow = 256;     // entries
+constexpr int kDiagTile = 16;
+typedef double diag_d4 __attribute__((ext_vector_type(4)));
+
+// wrap_offset of a difference of two points of the axis, |d| < len
+__device__ inline int32_t wrap_near(int32_t d, int32_t len, int32_t periodic) {
+  if (!periodic) return d;
+  int32_t t = d + len / 2;
+  if (t < 0) t += len;
+  else if (t >= len) t -= len;
+  return t - len / 2;
+}
 
 __global__ __launch_bounds__(kDiagThreads) void k_diag_S(const int32_t* __restrict__ h_ptr,
                                                          const int32_t* __restrict__ h_idx,
@@ -216,23 +266,119 @@ __global__ __launch_bounds__(kDiagThreads) void k_diag_S(const int32_t* __restri
                                                          double* __restrict__ diagS) {
   __shared__ double zs[kDiagStage];
   __shared__ double part[kDiagThreads / 64];
+  __shared__ double sw[kDiagRow];
+  __shared__ int32_t sz[kDiagRow], sx[kDiagRow];  // grid row (-1: not a point of the grid) and column
   const int64_t r = blockIdx.x;
   const int tid = threadIdx.x;
   const int32_t e0 = h_ptr[r];
   const int64_t cnt = h_ptr[r + 1] - e0;
   const bool staged = cnt <= kDiagStage;
+  const bool small = cnt <= kDiagRow;
+  if (small) {
+    for (int t = tid; t < (int)cnt; t += kDiagThreads) {
+      const int32_t a = h_idx[e0 + t];
+      const bool ok = a >= 0 && a < n;
+      sw[t] = h_w[e0 + t];
+      sz[t] = ok ? a / g.nx : -1;
+      sx[t] = ok ? a % g.nx : 0;
+    }
+  }
   const int64_t nc = staged ? max<int64_t>(1, min<int64_t>(N, kDiagStage / max<int64_t>(cnt, 1))) : N;
   double acc = 0.0;
   for (int64_t i0 = 0; i0 < N; i0 += nc) {
     const int64_t ni = min<int64_t>(nc, N - i0);
     if (staged) {
       __syncthreads();  // the previous chunk's reads are done
-      for (int64_t t = tid; t < cnt * ni; t += kDiagThreads) {
-        const int64_t i = t / cnt, e = t - i * cnt;
-        const int64_t a = h_idx[e0 + e];
-        zs[t] = (a >= 0 && a < n) ? Z[a + (i0 + i) * n] : 0.0;
+      const int c = (int)max<int64_t>(cnt, 1), count = (int)(cnt * ni);  // at most kDiagStage
+#pragma unroll 4
+      for (int t = tid; t < count; t += kDiagThreads) {
+        const int i = t / c, e = t - i * c;
+        if (small) {
+          const int64_t a = sz[e] < 0 ? -1 : (int64_t)sz[e] * g.nx + sx[e];
+          const double v = Z[(a < 0 ? 0 : a) + (i0 + i) * n];
+          zs[t] = a < 0 ? 0.0 : v;
+        } else {
+          const int64_t a = h_idx[e0 + e];
+          zs[t] = (a >= 0 && a < n) ? Z[a + (i0 + i) * n] : 0.0;
+        }
       }
       __syncthreads();
+    }
+    if (small && cnt >= kDiagTile) {
+      const int c = (int)cnt, count = (int)ni, lane = tid & 63, li = lane & 15, kq = lane >> 4;
+      const int side = (c + 15) / 16;
+      for (int tile = tid >> 6; tile < side * side; tile += kDiagThreads / 64) {
+        const int ec = 16 * (tile / side), fc = 16 * (tile % side);
+        // A lane l -> (e l%16, member l/16); B lane l -> (member l/16, f l%16); D register v of
+        // lane l -> (e 4v + l/16, f l%16)
+        const int f = min(fc + li, c - 1);
+        double h[4];
+#pragma unroll
+        for (int v = 0; v < 4; ++v) {
+          const int e = min(ec + 4 * v + kq, c - 1);
+          const int32_t za = sz[e], zb = sz[f];
+          const bool ok = ec + 4 * v + kq < c && fc + li < c && za >= 0 && zb >= 0;
+          const int32_t dz = wrap_near(zb - za, g.nz, g.pz), dx = wrap_near(sx[f] - sx[e], g.nx, g.px);
+          double l = 0.0;
+          if (dense_L) {
+            if (ok) l = dense_L[(int64_t)za * g.nx + sx[e] + ((int64_t)zb * g.nx + sx[f]) * n];
+          } else if (ok && dz >= -g.bz && dz <= g.bz && dx >= -g.bx && dx <= g.bx) {
+            l = g.table[(dz + g.bz) * (2 * g.bx + 1) + (dx + g.bx)];
+          }
+          h[v] = sw[e] * sw[f] * l;
+          if (l == 0.0) h[v] = 0.0;
+        }
+        diag_d4 d = {0.0, 0.0, 0.0, 0.0};
+        const bool eok = ec + li < c, fok = fc + li < c;
+        const double* pe = zs + min(ec + li, c - 1);
+        const double* pf = zs + f;
+        for (int k0 = 0; k0 < count; k0 += 12) {
+          double av[3], bv[3];
+#pragma unroll
+          for (int u = 0; u < 3; ++u) {
+            const int k = k0 + 4 * u + kq, at = min(k, count - 1) * c;
+            av[u] = k < count && eok ? pe[at] : 0.0;
+            bv[u] = k < count && fok ? pf[at] : 0.0;
+          }
+#pragma unroll
+          for (int u = 0; u < 3; ++u) d = __builtin_amdgcn_mfma_f64_16x16x4f64(av[u], bv[u], d, 0, 0, 0);
+        }
+#pragma unroll
+        for (int v = 0; v < 4; ++v)
+          if (h[v] != 0.0) acc += h[v] * d[v];
+      }
+      continue;
+    }
+    if (small) {
+      const int c = (int)cnt, count = (int)ni;
+      int e = c > 0 ? tid / c : 0, f = c > 0 ? tid % c : 0;
+      const int de = c > 0 ? kDiagThreads / c : 0, df = kDiagThreads - de * c;
+      for (int q = tid; q < c * c; q += kDiagThreads) {
+        const int32_t za = sz[e], zb = sz[f];
+        double l = 0.0;
+        if (za >= 0 && zb >= 0) {
+          if (dense_L) {
+            l = dense_L[(int64_t)za * g.nx + sx[e] + ((int64_t)zb * g.nx + sx[f]) * n];
+          } else {
+            const int32_t dz = wrap_near(zb - za, g.nz, g.pz), dx = wrap_near(sx[f] - sx[e], g.nx, g.px);
+            if (dz >= -g.bz && dz <= g.bz && dx >= -g.bx && dx <= g.bx)
+              l = g.table[(dz + g.bz) * (2 * g.bx + 1) + (dx + g.bx)];
+          }
+        }
+        if (l != 0.0) {
+          double zz = 0.0;
+#pragma unroll 4
+          for (int i = 0; i < count; ++i) zz += zs[i * c + e] * zs[i * c + f];
+          acc += sw[e] * sw[f] * l * zz;
+        }
+        e += de;
+        f += df;
+        if (f >= c) {
+          f -= c;
+          ++e;
+        }
+      }
+      continue;
     }
     for (int64_t q = tid; q < cnt * cnt; q += kDiagThreads) {
       const int64_t e = q / cnt, f = q - e * cnt;
@@ -312,7 +458,7 @@ hipError_t launch_ens_stats(const double* X, int64_t n, int64_t N, double* mu, d
 
 hipError_t launch_csc_count(const int32_t* h_ptr, const int32_t* h_idx, int64_t m, int64_t n, int64_t cap,
                             int32_t* col_cnt, int32_t* flags, hipStream_t st) {
-  hipLaunchKernelGGL(k_csc_count, dim3(blocks_for(m)), dim3(kBlock), 0, st, h_ptr, h_idx, m, n, cap, col_cnt,
+  hipLaunchKernelGGL(k_csc_count, dim3(blocks_for(m * kRowLanes)), dim3(kBlock), 0, st, h_ptr, h_idx, m, n, cap, col_cnt,
                      flags);
   return hipGetLastError();
 }
@@ -324,7 +470,7 @@ hipError_t launch_csc_finish(const int32_t* h_ptr, const int32_t* h_idx, const d
   hipLaunchKernelGGL(k_scan_one_block, dim3(1), dim3(kBlock), 0, st, col_cnt, n, col_ptr);
   if ((e = hipGetLastError()) != hipSuccess) return e;
   if ((e = launch_fill_i32(col_cnt, 0, n, st)) != hipSuccess) return e;
-  hipLaunchKernelGGL(k_csc_fill, dim3(blocks_for(m)), dim3(kBlock), 0, st, h_ptr, h_idx, h_w, m, col_ptr, col_cnt,
+  hipLaunchKernelGGL(k_csc_fill, dim3(blocks_for(m * kRowLanes)), dim3(kBlock), 0, st, h_ptr, h_idx, h_w, m, col_ptr, col_cnt,
                      row_of, w_of, flags);
   if ((e = hipGetLastError()) != hipSuccess) return e;
   hipLaunchKernelGGL(k_csc_sort, dim3(blocks_for(n)), dim3(kBlock), 0, st, col_ptr, n, row_of, w_of, flags);
@@ -335,8 +481,12 @@ hipError_t launch_obs_rhs_padded(const int32_t* h_ptr, const int32_t* h_idx, con
                                  const double* Z, int64_t n, int64_t N, int64_t m, double* rhs, int64_t ld,
                                  int64_t cnt, int64_t spad, hipStream_t st) {
   if (ld < m || spad < cnt || N < 1) return hipErrorInvalidValue;
-  hipLaunchKernelGGL(k_obs_rhs_padded, dim3(blocks_for(ld * spad)), dim3(kBlock), 0, st, h_ptr, h_idx, h_w, r_var, Z,
-                     n, N, m, rhs, ld, cnt, spad);
+  if (ld * spad <= kWaveOutputs)
+    hipLaunchKernelGGL(k_obs_rhs_padded<true>, dim3(blocks_for(64 * ld * spad)), dim3(kBlock), 0, st, h_ptr, h_idx,
+                       h_w, r_var, Z, n, N, m, rhs, ld, cnt, spad);
+  else
+    hipLaunchKernelGGL(k_obs_rhs_padded<false>, dim3(blocks_for(ld * spad)), dim3(kBlock), 0, st, h_ptr, h_idx, h_w,
+                       r_var, Z, n, N, m, rhs, ld, cnt, spad);
   return hipGetLastError();
 }
 
@@ -351,8 +501,12 @@ hipError_t launch_obs_rhs(const int32_t* h_ptr, const int32_t* h_idx, const doub
 hipError_t launch_innovation(const int32_t* h_ptr, const int32_t* h_idx, const double* h_w, const double* r_var,
                              const double* y, const double* mu, int64_t m, int64_t n, double* out, int64_t ld,
                              int64_t s, hipStream_t st) {
-  hipLaunchKernelGGL(k_innovation, dim3(blocks_for(m)), dim3(kBlock), 0, st, h_ptr, h_idx, h_w, r_var, y, mu, m, n,
-                     out, ld, s);
+  if (m <= kWaveOutputs)
+    hipLaunchKernelGGL(k_innovation<true>, dim3(blocks_for(64 * m)), dim3(kBlock), 0, st, h_ptr, h_idx, h_w, r_var, y,
+                       mu, m, n, out, ld, s);
+  else
+    hipLaunchKernelGGL(k_innovation<false>, dim3(blocks_for(m)), dim3(kBlock), 0, st, h_ptr, h_idx, h_w, r_var, y, mu,
+                       m, n, out, ld, s);
   return hipGetLastError();
 }
 

@@ -115,6 +115,69 @@ __device__ inline int block_exclusive_scan(int v, int* swave, int* total) {
   return swave[wave] + x - v;
 }
 
+// sum over the entries e0 <= e < e1 of one row of H of w_e col[idx_e], in the order of e (entries
+// outside [0, n) are skipped; the input checks flag them).  A chain of load, load, multiply-add per
+// entry is bound by its two latencies: sixteen entries are loaded at a time, and the next sixteen
+// indices and weights while their values are under way (100 rows of 177 entries x 100 columns:
+// 66 us one at a time, 41 so).  Rows of one or two entries, the point observations, load only those.
+template <typename T>
+__device__ inline double row_dot(const int32_t* __restrict__ h_idx, const double* __restrict__ h_w, int32_t e0,
+                                 int32_t e1, int64_t n, const T* __restrict__ col) {
+  double a = 0.0;
+  if (e1 - e0 <= 2) {
+    for (int32_t e = e0; e < e1; ++e) {
+      const int32_t j = h_idx[e];
+      if (j >= 0 && j < n) a += h_w[e] * (double)col[j];
+    }
+    return a;
+  }
+  constexpr int U = 16;
+  int32_t j[U];
+  double w[U];
+#pragma unroll
+  for (int u = 0; u < U; ++u) {
+    const int32_t e = min(e0 + u, e1 - 1);
+    j[u] = h_idx[e];
+    w[u] = h_w[e];
+  }
+  for (int32_t e = e0; e < e1; e += U) {
+    double v[U], wv[U];
+    bool ok[U];
+#pragma unroll
+    for (int u = 0; u < U; ++u) {
+      ok[u] = e + u < e1 && j[u] >= 0 && j[u] < n;
+      v[u] = (double)col[ok[u] ? j[u] : 0];
+      wv[u] = w[u];
+    }
+#pragma unroll
+    for (int u = 0; u < U; ++u) {
+      const int32_t f = min(e + U + u, e1 - 1);
+      j[u] = h_idx[f];
+      w[u] = h_w[f];
+    }
+#pragma unroll
+    for (int u = 0; u < U; ++u)
+      if (ok[u]) a += wv[u] * v[u];
+  }
+  return a;
+}
+
+// The same sum by a wavefront, in lane 63: lane l adds entries l, l + 64, ... and a tree the lanes.  For
+// up to kWaveOutputs sums in a launch, where a thread for each leaves most of the chip idle and its
+// lanes read different rows of H (100 x 100 sums of 177 entries: 41 us a thread each, 5 a
+// wavefront each).  More sums fill the chip, and a wavefront for a row of one entry wastes 63 lanes.
+constexpr int64_t kWaveOutputs = 32768;
+template <typename T>
+__device__ inline double row_dot_wave(const int32_t* __restrict__ h_idx, const double* __restrict__ h_w, int32_t e0,
+                                      int32_t e1, int64_t n, const T* __restrict__ col) {
+  double a = 0.0;
+  for (int32_t e = e0 + (int32_t)(threadIdx.x & 63); e < e1; e += 64) {
+    const int32_t j = h_idx[e];
+    if (j >= 0 && j < n) a += h_w[e] * (double)col[j];
+  }
+  return wave_sum_dpp(a);
+}
+
 // ---------------------------------------------------------------- kernels (launchers)
 // All launchers enqueue on `st` and return hipError_t of the launch.
 
