@@ -30,7 +30,7 @@ __global__ void k_unit_cols(int64_t rows, int64_t j0, int64_t bc, double* __rest
 
 // V[:, c] = H^T R^{-1/2} e_{j0 + c}: row j0 + c of H, scaled by r^{-1/2}, on a zeroed state
 // column.  One wavefront per column (a thread per column took 61 us for rows of 177 entries, now
-// TBD); repeated indices, which the input checks flag, sum in any order.
+// 4.5); repeated indices, which the input checks flag, sum in any order.
 __global__ __launch_bounds__(256) void k_scatter_unit_obs(const int32_t* __restrict__ h_ptr,
                                                           const int32_t* __restrict__ h_idx,
                                                           const double* __restrict__ h_w,
