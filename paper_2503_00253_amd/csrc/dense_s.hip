@@ -48,30 +48,32 @@ __global__ __launch_bounds__(256) void k_scatter_unit_obs(const int32_t* __restr
 }
 
 // S[(j0 + c) * lds + r] = (S e_{j0+c})_r from the apply output T: the observation-domain
-// output itself, or R^{-1/2} H T for a state-domain output.  WAVE: a wavefront per entry
-// (kWaveOutputs).
-template <bool WAVE>
+// output itself, or R^{-1/2} H T for a state-domain output.
 __global__ void k_gather_s_cols(int obs_domain, const double* __restrict__ T, int64_t ldt,
                                 const int32_t* __restrict__ h_ptr, const int32_t* __restrict__ h_idx,
                                 const double* __restrict__ h_w, const double* __restrict__ r_var, int64_t n,
                                 int64_t m, int64_t j0, int64_t bc, double* __restrict__ S, int64_t lds) {
-  int64_t t = blockIdx.x * (int64_t)blockDim.x + threadIdx.x;
-  if (WAVE) t /= 64;
+  const int64_t t = blockIdx.x * (int64_t)blockDim.x + threadIdx.x;
   if (t >= m * bc) return;
   const int64_t c = t / m, r = t - c * m;
   const double* col = T + c * ldt;
-  if (WAVE) {  // the state domain
-    const double w = row_dot_wave(h_idx, h_w, h_ptr[r], h_ptr[r + 1], n, col) / sqrt(r_var[r]);
-    if ((threadIdx.x & 63) == 63) S[(j0 + c) * lds + r] = w;
-    return;
-  }
-  double v;
-  if (obs_domain) {
-    v = col[r];
-  } else {
-    v = row_dot(h_idx, h_w, h_ptr[r], h_ptr[r + 1], n, col) / sqrt(r_var[r]);
-  }
-  S[(j0 + c) * lds + r] = v;
+  S[(j0 + c) * lds + r] =
+      obs_domain ? col[r] : row_dot(h_idx, h_w, h_ptr[r], h_ptr[r + 1], n, col) / sqrt(r_var[r]);
+}
+
+// The same for a state-domain output, a workgroup for a row and 64 columns (up to kRowOutputs entries).
+__global__ __launch_bounds__(64) void k_gather_s_rows(const double* __restrict__ T, int64_t ldt,
+                                                      const int32_t* __restrict__ h_ptr,
+                                                      const int32_t* __restrict__ h_idx,
+                                                      const double* __restrict__ h_w,
+                                                      const double* __restrict__ r_var, int64_t n, int64_t j0,
+                                                      int64_t bc, double* __restrict__ S, int64_t lds) {
+  __shared__ int32_t sj[kRowChunk];
+  __shared__ double sw[kRowChunk];
+  const int64_t r = blockIdx.x, c = (int64_t)blockIdx.y * 64 + threadIdx.x;
+  const double* col = T + (c < bc ? c : 0) * ldt;
+  const double v = row_dot_shared(h_idx, h_w, h_ptr[r], h_ptr[r + 1], n, col, sj, sw) / sqrt(r_var[r]);
+  if (c < bc) S[(j0 + c) * lds + r] = v;
 }
 
 // S <- (S + S^T) / 2 (S is symmetric in exact arithmetic; its columns come from separate
@@ -166,12 +168,12 @@ hipError_t launch_gather_s_cols(int obs_domain, const double* T, int64_t ldt, co
                                 const int32_t* h_idx, const double* h_w, const double* r_var, int64_t n, int64_t m,
                                 int64_t j0, int64_t bc, double* S, int64_t lds, hipStream_t st) {
   if (m <= 0 || bc <= 0) return hipSuccess;
-  if (!obs_domain && m * bc <= kWaveOutputs)
-    hipLaunchKernelGGL(k_gather_s_cols<true>, dim3(nblocks(64 * m * bc)), dim3(256), 0, st, obs_domain, T, ldt, h_ptr,
-                       h_idx, h_w, r_var, n, m, j0, bc, S, lds);
+  if (!obs_domain && m * bc <= kRowOutputs)
+    hipLaunchKernelGGL(k_gather_s_rows, dim3((unsigned)m, (unsigned)((bc + 63) / 64)), dim3(64), 0, st, T, ldt, h_ptr,
+                       h_idx, h_w, r_var, n, j0, bc, S, lds);
   else
-    hipLaunchKernelGGL(k_gather_s_cols<false>, dim3(nblocks(m * bc)), dim3(256), 0, st, obs_domain, T, ldt, h_ptr,
-                       h_idx, h_w, r_var, n, m, j0, bc, S, lds);
+    hipLaunchKernelGGL(k_gather_s_cols, dim3(nblocks(m * bc)), dim3(256), 0, st, obs_domain, T, ldt, h_ptr, h_idx, h_w,
+                       r_var, n, m, j0, bc, S, lds);
   return hipGetLastError();
 }
 

@@ -180,27 +180,32 @@ __global__ void k_obs_rhs(const int32_t* __restrict__ h_ptr, const int32_t* __re
 }
 
 // The same for systems 0 .. cnt-1 over the whole ld x spad block: zeros in the padding rows
-// (r >= m) and padding systems (s >= cnt).  WAVE: a wavefront per entry (kWaveOutputs).
-template <bool WAVE>
+// (r >= m) and padding systems (s >= cnt).
 __global__ void k_obs_rhs_padded(const int32_t* __restrict__ h_ptr, const int32_t* __restrict__ h_idx,
                                  const double* __restrict__ h_w, const double* __restrict__ r_var,
                                  const double* __restrict__ Z, int64_t n, int64_t N, int64_t m,
                                  double* __restrict__ rhs, int64_t ld, int64_t cnt, int64_t spad) {
-  int64_t t = blockIdx.x * (int64_t)blockDim.x + threadIdx.x;
-  if (WAVE) t /= 64;
+  const int64_t t = blockIdx.x * (int64_t)blockDim.x + threadIdx.x;
   if (t >= ld * spad) return;
   const int64_t c = t / ld, r = t % ld;
-  if (WAVE) {
-    double v = 0.0;
-    if (c < cnt && r < m)
-      v = row_dot_wave(h_idx, h_w, h_ptr[r], h_ptr[r + 1], n, Z + (c % N) * n) / sqrt(r_var[r]);
-    if ((threadIdx.x & 63) == 63) rhs[t] = v;
-    return;
-  }
   rhs[t] = (c < cnt && r < m) ? obs_rhs_entry(h_ptr, h_idx, h_w, r_var, Z, n, r, c % N) : 0.0;
 }
 
-// R^{-1/2} (y - H mu), WAVE as above
+// The same, a workgroup for a row and 64 systems (up to kRowOutputs entries).
+__global__ __launch_bounds__(64) void k_obs_rhs_rows(const int32_t* __restrict__ h_ptr,
+                                                     const int32_t* __restrict__ h_idx,
+                                                     const double* __restrict__ h_w, const double* __restrict__ r_var,
+                                                     const double* __restrict__ Z, int64_t n, int64_t N, int64_t m,
+                                                     double* __restrict__ rhs, int64_t ld, int64_t cnt, int64_t spad) {
+  __shared__ int32_t sj[kRowChunk];
+  __shared__ double sw[kRowChunk];
+  const int64_t r = blockIdx.x, c = (int64_t)blockIdx.y * 64 + threadIdx.x;
+  double v = 0.0;
+  if (r < m) v = row_dot_shared(h_idx, h_w, h_ptr[r], h_ptr[r + 1], n, Z + (c % N) * n, sj, sw) / sqrt(r_var[r]);
+  if (c < spad) rhs[c * ld + r] = c < cnt ? v : 0.0;
+}
+
+// R^{-1/2} (y - H mu); WAVE: a wavefront per entry (up to kRowOutputs)
 template <bool WAVE>
 __global__ void k_innovation(const int32_t* __restrict__ h_ptr, const int32_t* __restrict__ h_idx,
                              const double* __restrict__ h_w, const double* __restrict__ r_var,
@@ -481,12 +486,12 @@ hipError_t launch_obs_rhs_padded(const int32_t* h_ptr, const int32_t* h_idx, con
                                  const double* Z, int64_t n, int64_t N, int64_t m, double* rhs, int64_t ld,
                                  int64_t cnt, int64_t spad, hipStream_t st) {
   if (ld < m || spad < cnt || N < 1) return hipErrorInvalidValue;
-  if (ld * spad <= kWaveOutputs)
-    hipLaunchKernelGGL(k_obs_rhs_padded<true>, dim3(blocks_for(64 * ld * spad)), dim3(kBlock), 0, st, h_ptr, h_idx,
+  if (ld * spad <= kRowOutputs)
+    hipLaunchKernelGGL(k_obs_rhs_rows, dim3((unsigned)ld, (unsigned)((spad + 63) / 64)), dim3(64), 0, st, h_ptr, h_idx,
                        h_w, r_var, Z, n, N, m, rhs, ld, cnt, spad);
   else
-    hipLaunchKernelGGL(k_obs_rhs_padded<false>, dim3(blocks_for(ld * spad)), dim3(kBlock), 0, st, h_ptr, h_idx, h_w,
-                       r_var, Z, n, N, m, rhs, ld, cnt, spad);
+    hipLaunchKernelGGL(k_obs_rhs_padded, dim3(blocks_for(ld * spad)), dim3(kBlock), 0, st, h_ptr, h_idx, h_w, r_var, Z,
+                       n, N, m, rhs, ld, cnt, spad);
   return hipGetLastError();
 }
 
@@ -501,7 +506,7 @@ hipError_t launch_obs_rhs(const int32_t* h_ptr, const int32_t* h_idx, const doub
 hipError_t launch_innovation(const int32_t* h_ptr, const int32_t* h_idx, const double* h_w, const double* r_var,
                              const double* y, const double* mu, int64_t m, int64_t n, double* out, int64_t ld,
                              int64_t s, hipStream_t st) {
-  if (m <= kWaveOutputs)
+  if (m <= kRowOutputs)
     hipLaunchKernelGGL(k_innovation<true>, dim3(blocks_for(64 * m)), dim3(kBlock), 0, st, h_ptr, h_idx, h_w, r_var, y,
                        mu, m, n, out, ld, s);
   else

@@ -162,20 +162,69 @@ __device__ inline double row_dot(const int32_t* __restrict__ h_idx, const double
   return a;
 }
 
-// The same sum by a wavefront, in lane 63: lane l adds entries l, l + 64, ... and a tree the lanes.  For
-// up to kWaveOutputs sums in a launch, where a thread for each leaves most of the chip idle and its
-// lanes read different rows of H (100 x 100 sums of 177 entries: 41 us a thread each, 5 a
-// wavefront each).  More sums fill the chip, and a wavefront for a row of one entry wastes 63 lanes.
-constexpr int64_t kWaveOutputs = 32768;
+// The sums of one row of H with 64 columns, a column a lane of a 64-thread workgroup: the same chain as
+// row_dot's.  The row's indices and weights are read once into LDS for all lanes, and sixteen of a
+// lane's values are in flight; lanes whose outputs are other rows of H read every index apart.  For up
+// to kRowOutputs sums in a launch, where a thread for each also leaves most of the chip idle (100 x 100
+// sums of 177 entries: 41 us a thread each, 17 so); more sums fill the chip, and rows of one entry
+// then write and read along the rows.
+constexpr int64_t kRowOutputs = 32768;
+constexpr int kRowChunk = 64;
 template <typename T>
-__device__ inline double row_dot_wave(const int32_t* __restrict__ h_idx, const double* __restrict__ h_w, int32_t e0,
-                                      int32_t e1, int64_t n, const T* __restrict__ col) {
+__device__ inline double row_dot_shared(const int32_t* __restrict__ h_idx, const double* __restrict__ h_w, int32_t e0,
+                                        int32_t e1, int64_t n, const T* __restrict__ col, int32_t* sj, double* sw) {
   double a = 0.0;
-  for (int32_t e = e0 + (int32_t)(threadIdx.x & 63); e < e1; e += 64) {
+  const int lane = threadIdx.x;
+  for (int32_t c0 = e0; c0 < e1; c0 += kRowChunk) {
+    const int32_t e = min(c0 + lane, e1 - 1);
     const int32_t j = h_idx[e];
-    if (j >= 0 && j < n) a += h_w[e] * (double)col[j];
+    const double w = h_w[e];
+    __syncthreads();  // the previous chunk's reads are done
+    sj[lane] = c0 + lane < e1 && j >= 0 && j < n ? j : -1;
+    sw[lane] = w;
+    __syncthreads();
+    const int cnt = min(kRowChunk, e1 - c0);
+    for (int u0 = 0; u0 < cnt; u0 += 16) {
+      double v[16];
+#pragma unroll
+      for (int u = 0; u < 16; ++u) {
+        const int32_t ju = sj[u0 + u];
+        v[u] = (double)col[ju < 0 ? 0 : ju];
+      }
+#pragma unroll
+      for (int u = 0; u < 16; ++u)
+        if (sj[u0 + u] >= 0) a += sw[u0 + u] * v[u];
+    }
   }
-  return wave_sum_dpp(a);
+  return a;
+}
+
+// The same chain for one sum by a wavefront: its lanes bring the products' factors 64 at a time, every
+// lane adds them in order (a thread alone 21 us for 177 entries, 13 so).
+__device__ inline double row_dot_wave(const int32_t* __restrict__ h_idx, const double* __restrict__ h_w, int32_t e0,
+                                      int32_t e1, int64_t n, const double* __restrict__ col) {
+  auto from = [](double x, int l) {
+    const long long b = __builtin_bit_cast(long long, x);
+    const int lo = __builtin_amdgcn_readlane((int)(b & 0xffffffffll), l);
+    const int hi = __builtin_amdgcn_readlane((int)(b >> 32), l);
+    return __builtin_bit_cast(double, ((long long)hi << 32) | (unsigned)lo);
+  };
+  double a = 0.0;
+  for (int32_t c0 = e0; c0 < e1; c0 += 64) {
+    const int32_t e = min(c0 + (int32_t)(threadIdx.x & 63), e1 - 1);
+    const int32_t j = h_idx[e];
+    const bool ok = j >= 0 && j < n;
+    const double w = h_w[e], v = col[ok ? j : 0];
+    const unsigned long long valid = __ballot(ok && c0 + (int32_t)(threadIdx.x & 63) < e1);
+    for (int u0 = 0; u0 < min(64, e1 - c0); u0 += 8) {
+#pragma unroll
+      for (int u = 0; u < 8; ++u) {
+        const double s = fma(from(w, u0 + u), from(v, u0 + u), a);
+        a = valid >> (u0 + u) & 1 ? s : a;
+      }
+    }
+  }
+  return a;
 }
 
 // ---------------------------------------------------------------- kernels (launchers)

@@ -1,4 +1,4 @@
-"""Observation rows of many entries on the GPU: the row sums a wavefront or sixteen entries at a time,
+"""Observation rows of many entries on the GPU: the row sums a workgroup, a wavefront or a thread each,
 the CSC copy, the dense S and diag(S) by tiles, at the edges of their chunks (2 and 16 entries, a
 wavefront, one and several tiles, rows past the tiled kernel's 256), against the FP64 oracle.
 
