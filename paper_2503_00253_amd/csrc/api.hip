@@ -497,9 +497,8 @@ struct Sys {
 
 struct Pre {
   int k = 0, p = 0;
-  double *Om = nullptr, *Y = nullptr, *Qb = nullptr, *SQ = nullptr, *Tk = nullptr, *evec = nullptr,
-         *evals = nullptr, *Rinv = nullptr, *sel = nullptr, *Phi = nullptr, *SPhi = nullptr, *theta = nullptr,
-         *G = nullptr, *gscr = nullptr, *sig = nullptr;
+  double *Om = nullptr, *Y = nullptr, *Qb = nullptr, *SQ = nullptr, *Tk = nullptr, *Rinv = nullptr, *sel = nullptr,
+         *Phi = nullptr, *SPhi = nullptr, *theta = nullptr, *G = nullptr, *gscr = nullptr, *sig = nullptr;
   int32_t *act = nullptr, *nact = nullptr;
 };
 
@@ -811,8 +810,6 @@ void plan_layout(Plan& pl, Arena& ar, const infoesrf_problem* P, const Options& 
     pr.Qb = ar.take<double>(sy.ldm * kl);
     pr.SQ = ar.take<double>(sy.ldm * kl);
     pr.Tk = ar.take<double>(op.k * op.k);
-    pr.evec = ar.take<double>(op.k * op.k);
-    pr.evals = ar.take<double>(op.k);
     pr.Rinv = ar.take<double>(op.k * op.k);
     pr.sel = ar.take<double>(op.k * op.p);
     pr.Phi = ar.take<double>(sy.ldm * op.p);
@@ -1163,7 +1160,7 @@ int stage_precond(Plan& pl, const Options& op, hipStream_t st) {
     IE_HIP(launch_ritz_small(pr.Qb, pr.SQ, in.m, k, pr.p, ldm, pr.theta, pr.Phi, pr.SPhi, pr.G, st));
     return 0;
   }
-  // Cholesky-QR twice: Qb = Y R^{-1}
+  // Cholesky-QR twice: Q = (Y R^{-1}) R^{-1}, which ends in Y
   const Strided Ys{pr.Y, 1, ldm}, Qs{pr.Qb, 1, ldm};
   IE_HIP(launch_gram(Ys, Ys, in.m, k, pr.Rinv, pr.gscr, st));
   IE_HIP(launch_chol_inv(pr.Rinv, k, in.flags, st));
@@ -1171,19 +1168,14 @@ int stage_precond(Plan& pl, const Options& op, hipStream_t st) {
   IE_HIP(launch_gram(Qs, Qs, in.m, k, pr.Rinv, pr.gscr, st));
   IE_HIP(launch_chol_inv(pr.Rinv, k, in.flags, st));
   IE_HIP(launch_right_mult(Qs, in.m, k, pr.Rinv, k, pr.Y, 1, ldm, st));
-  IE_HIP(launch_copy_cols(pr.Y, ldm, ldm, k, pr.Qb, ldm, st));
-  IE_TRY(apply_S(pl, Prec::F64, pr.Qb, ldm, pr.act, pr.nact, k, pr.sig, pr.SQ, op.rows_per_wave, st));
+  IE_TRY(apply_S(pl, Prec::F64, pr.Y, ldm, pr.act, pr.nact, k, pr.sig, pr.SQ, op.rows_per_wave, st));
   const Strided SQs{pr.SQ, 1, ldm};
-  IE_HIP(launch_gram(Qs, SQs, in.m, k, pr.Tk, pr.gscr, st));
-  IE_HIP(launch_sym_eig(pr.Tk, k, pr.evec, pr.evals, st));
-  IE_HIP(launch_lmp_finish(pr.evals, pr.evec, k, pr.p, pr.theta, pr.sel, st));
+  IE_HIP(launch_gram(Ys, SQs, in.m, k, pr.Tk, pr.gscr, st));
+  IE_HIP(launch_sym_eig(pr.Tk, k, pr.p, pr.theta, pr.sel, st));
   const int p = pr.p;
-  IE_HIP(launch_right_mult(Qs, in.m, k, pr.sel, p, pr.Phi, 1, ldm, st));  // column-major m x p, ld = ldm
-  IE_HIP(launch_right_mult(SQs, in.m, k, pr.sel, p, pr.SPhi, 1, ldm, st));
-  const Strided Ph{pr.Phi, 1, ldm}, SPh{pr.SPhi, 1, ldm};
-  IE_HIP(launch_gram(Ph, Ph, in.m, p, pr.G, pr.gscr, st));
-  IE_HIP(launch_gram(Ph, SPh, in.m, p, pr.G + p * p, pr.gscr, st));
-  IE_HIP(launch_gram(SPh, SPh, in.m, p, pr.G + 2 * p * p, pr.gscr, st));
+  // column-major m x p, ld = ldm
+  IE_HIP(launch_right_mult(Ys, in.m, k, pr.sel, p, pr.Phi, 1, ldm, st, &SQs, pr.SPhi));
+  IE_HIP(launch_gram_pair(Strided{pr.Phi, 1, ldm}, Strided{pr.SPhi, 1, ldm}, in.m, p, pr.G, pr.gscr, st));
   return 0;
 }
 

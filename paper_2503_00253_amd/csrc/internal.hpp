@@ -634,15 +634,16 @@ hipError_t launch_sketch_setup(uint64_t seed, int64_t m, int k, double* out, int
                                double* sig, int nsig, hipStream_t st);
 // Gram: G[a*k+b] = sum_r A(r, a) B(r, b), a,b < k (fixed order, deterministic)
 hipError_t launch_gram(Strided A, Strided B, int64_t m, int k, double* G, double* scratch, hipStream_t st);
+// A^T A, A^T B, B^T B (k x k each) into G, one after the other; scratch as launch_gram's
+hipError_t launch_gram_pair(Strided A, Strided B, int64_t m, int k, double* G, double* scratch, hipStream_t st);
 int gram_chunks(int64_t m);  // row chunks of launch_gram: scratch holds gram_chunks(m) * k * k doubles
 // One-workgroup small dense kernels.
 hipError_t launch_chol_inv(double* G, int k, int32_t* flags, hipStream_t st);   // G <- R^{-1} (upper), G = R^T R
-// out(r, j) = sum_a A(r, a) M[a*kout + j], out(r, j) at out[r*ors + j*ocs]
+// out(r, j) = sum_a A(r, a) M[a*kout + j], out(r, j) at out[r*ors + j*ocs]; A2 (nullable) likewise into out2
 hipError_t launch_right_mult(Strided A, int64_t m, int k, const double* M, int kout, double* out, int64_t ors,
-                             int64_t ocs, hipStream_t st);
-hipError_t launch_sym_eig(double* T, int k, double* evec, double* evals, hipStream_t st);  // Jacobi
-hipError_t launch_lmp_finish(const double* evals, const double* evec, int k, int p, double* theta, double* sel,
-                             hipStream_t st);                                  // top-p selection matrix
+                             int64_t ocs, hipStream_t st, const Strided* A2 = nullptr, double* out2 = nullptr);
+// Jacobi: the p largest eigenvalues of T (k x k) and the k x p matrix of their eigenvectors
+hipError_t launch_sym_eig(const double* T, int k, int p, double* theta, double* sel, hipStream_t st);
 hipError_t launch_min_reduce(const double* v, int64_t count, double* out, hipStream_t st);
 // The setup's small dense steps for k <= 8 sketch columns and m <= 8192 rows in two launches:
 // Q = orth(Y) by Cholesky-QR twice, then theta, Phi, S Phi and the three Gram blocks from Qb and

@@ -106,6 +106,7 @@ __global__ void k_gram_reduce(const double* __restrict__ scratch, int nchunks, i
   const int t = blockIdx.x * blockDim.x + threadIdx.x;
   if (t >= k * k) return;
   double acc = 0.0;
+#pragma unroll 16  // loads in flight; the sum in the order of the chunks
   for (int c = 0; c < nchunks; ++c) acc += scratch[(int64_t)c * k * k + t];
   G[t] = acc;
 }
@@ -118,128 +119,160 @@ constexpr double kCholDrop = 1e-12;
 
 // G (k x k, row-major, symmetric PSD) -> inverse of its upper Cholesky factor R (G = R^T R), in
 // place, with dependent columns (pivot <= kCholDrop max diag G) given zero rows in R and zero
-// columns in R^{-1}.  A non-finite pivot sets the numeric flag.  One wavefront; the inverse's
-// columns are built in LDS.
-__global__ void k_chol_inv(double* G, int k, int32_t* flags) {
+// columns in R^{-1}.  A non-finite pivot sets the numeric flag.  One wavefront, lane c on column c of
+// R and of the inverse: bound by the chain of k pivots (a square root and a division each) and of k
+// back-substitution steps, so the entries of four rows are read ahead of their multiply-adds and no
+// lane divides to find its entry.
+__global__ __launch_bounds__(64) void k_chol_inv(double* G, int k, int32_t* flags) {
+  static_assert(kMaxSketch <= 64, "a column a lane");
   __shared__ double R[kMaxSketch * kMaxSketch];
   __shared__ double X[kMaxSketch * kMaxSketch];
-  __shared__ int bad;
-  __shared__ double gmax;
   const int t = threadIdx.x;
-  if (t == 0) {
-    bad = 0;
-    double g = 0.0;
-    for (int j = 0; j < k; ++j) g = fmax(g, G[j * k + j]);
-    gmax = g;
-  }
-  for (int e = t; e < k * k; e += blockDim.x) R[e] = G[e];
+  const int c = min(t, k - 1);
+  double gmax = t < k ? fmax(0.0, G[t * k + t]) : 0.0;
+#pragma unroll 8
+  for (int e = t; e < k * k; e += 64) R[e] = G[e];
+  for (int off = 32; off > 0; off >>= 1) gmax = fmax(gmax, __shfl_xor(gmax, off, 64));
   __syncthreads();
   // right-looking Cholesky, column j
+  bool bad = false;
   for (int j = 0; j < k; ++j) {
-    if (t == 0) {
-      const double d = R[j * k + j];
-      if (!isfinite(d)) bad = 1;
-      R[j * k + j] = (d > kCholDrop * gmax) ? sqrt(d) : 0.0;
-    }
+    const double d = R[j * k + j], rc = R[j * k + c];
+    if (!isfinite(d)) bad = true;
+    const double rjj = (d > kCholDrop * gmax) ? sqrt(d) : 0.0;
+    const double rjc = rjj > 0.0 ? rc / rjj : 0.0;
     __syncthreads();
-    const double rjj = R[j * k + j];
-    for (int c = j + 1 + t; c < k; c += blockDim.x) R[j * k + c] = rjj > 0.0 ? R[j * k + c] / rjj : 0.0;
+    if (t == j) R[j * k + j] = rjj;
+    if (t > j && t < k) R[j * k + t] = rjc;
     __syncthreads();
-    for (int e = t; e < (k - j - 1) * (k - j - 1); e += blockDim.x) {
-      const int a = j + 1 + e / (k - j - 1), b = j + 1 + e % (k - j - 1);
-      if (b >= a) R[a * k + b] -= R[j * k + a] * R[j * k + b];
+    for (int a0 = j + 1; a0 < k; a0 += 4) {
+      double ra[4], rr[4];
+#pragma unroll
+      for (int u = 0; u < 4; ++u) {
+        const int a = min(a0 + u, k - 1);
+        ra[u] = R[j * k + a];
+        rr[u] = R[a * k + c];
+      }
+#pragma unroll
+      for (int u = 0; u < 4; ++u)
+        if (a0 + u < k && t < k && t >= a0 + u) R[(a0 + u) * k + c] = rr[u] - ra[u] * rjc;
     }
     __syncthreads();
   }
   // R is upper triangular in R[a*k+b], b >= a.  Invert by columns: Rinv[:, c] solves R x = e_c
-  // (X[a*k + c] = x_a, written by the thread of column c only); x_a = 0 on a dropped row.
-  for (int c = t; c < k; c += blockDim.x) {
+  // (X[a*k + c] = x_a, written and read by the lane of column c only); x_a = 0 on a dropped row.
+  if (t < k) {
     for (int a = k - 1; a >= 0; --a) {
       double s = (a == c) ? 1.0 : 0.0;
-      for (int b = a + 1; b < k; ++b) s -= R[a * k + b] * X[b * k + c];
-      X[a * k + c] = (a <= c && R[a * k + a] > 0.0) ? s / R[a * k + a] : 0.0;
+      const double raa = R[a * k + a];
+      for (int b0 = a + 1; b0 < k; b0 += 4) {
+        double rb[4], xb[4];
+#pragma unroll
+        for (int u = 0; u < 4; ++u) {
+          const int b = min(b0 + u, k - 1);
+          rb[u] = R[a * k + b];
+          xb[u] = X[b * k + c];
+        }
+#pragma unroll
+        for (int u = 0; u < 4; ++u)
+          if (b0 + u < k) s -= rb[u] * xb[u];
+      }
+      X[a * k + c] = (a <= c && raa > 0.0) ? s / raa : 0.0;
     }
   }
   __syncthreads();
-  for (int e = t; e < k * k; e += blockDim.x) G[e] = X[e];
+  for (int e = t; e < k * k; e += 64) G[e] = X[e];
   if (t == 0 && bad) atomicOr(flags, kFlagNumeric);
 }
 
-// out(r, j) = sum_a A(r, a) M[a*kout + j]
-__global__ void k_right_mult(Strided A, int64_t m, int k, const double* __restrict__ M, int kout,
-                             double* __restrict__ out, int64_t ors, int64_t ocs) {
+// out(r, j) = sum_a A(r, a) M[a*kout + j]; the second row of blocks takes A2 into out2
+__global__ void k_right_mult(Strided A, Strided A2, int64_t m, int k, const double* __restrict__ M, int kout,
+                             double* __restrict__ out, double* __restrict__ out2, int64_t ors, int64_t ocs) {
   const int64_t t = blockIdx.x * (int64_t)blockDim.x + threadIdx.x;
   if (t >= m * kout) return;
+  if (blockIdx.y) {
+    A = A2;
+    out = out2;
+  }
   const int64_t r = t % m;
   const int j = (int)(t / m);
   double acc = 0.0;
+#pragma unroll 8  // loads in flight; the sum in the order of a
   for (int a = 0; a < k; ++a) acc += A.ptr[r * A.rs + a * A.cs] * M[a * kout + j];
   out[r * ors + j * ocs] = acc;
 }
 
 // Jacobi eigendecomposition of a small symmetric matrix on one workgroup with the round-robin
 // (tournament) ordering: each step rotates k/2 disjoint index pairs at once, k-1 steps make a
-// sweep in which every pair is visited once.  A step is two phases: the rotations of the pairs,
-// then, with A double-buffered, every thread's 2 x 2 blocks of the next A = J^T A J (one block
-// per pair of pairs) and its pair of eigenvector entries (V J, in place: each pair of entries
-// has one owner).  T (k x k row-major) is read;
-// evec[a*k + j] = component a of eigenvector j.
-__device__ inline void jacobi_player(int slot, int step, int ke, int k, int* p, int* q, int t) {
-  // players: slot 0 fixed, slots 1..ke-1 rotate by `step`; pair t holds slots t and ke-1-t
-  auto player = [&](int sl) { return sl == 0 ? 0 : 1 + (sl - 1 + step) % (ke - 1); };
-  int a = player(t), b = player(ke - 1 - t);
-  if (a > b) {
-    const int tmp = a;
-    a = b;
-    b = tmp;
-  }
-  *p = a;
-  *q = b;
-  (void)slot;
-  (void)k;
-}
-
+// sweep in which every pair is visited once.  A step is the 2 x 2 blocks of the next A = J^T A J (A
+// double-buffered, one block per pair of pairs) and the pairs of eigenvector entries (V J, in place:
+// each pair of entries has one owner).  The thread of block (i1, i2) forms the rotations of both
+// pairs itself, two chains of square root, division and reciprocal root side by side: handing them
+// round in LDS was a second barrier and a second round of LDS reads in a step that is nothing but
+// latency and issue, so no address is multiplied out either (k = 20: 122 us, now 75; with the two
+// rotations behind branches, one after the other, 101).  T (k x k row-major) is read.
+//
+// The p largest eigenvalues then go to theta, and the selection matrix to sel (k x p, row-major):
+// its column j is the eigenvector of the j-th largest.  Lane i finds the rank of eigenvalue i
+// (descending; ties by index, as a stable sort orders them).
 // The rotation (c, s) that zeroes a_pq of the 2 x 2 block [a_pp a_pq; a_pq a_qq]: the smaller
 // root t of t^2 + 2 tau t - 1 = 0, tau = (a_qq - a_pp) / (2 a_pq), written as
 // t = sign(d) 2 a_pq / (|d| + sqrt(d^2 + 4 a_pq^2)): one square root and one division.
-__device__ inline void jacobi_cs(double app, double aqq, double apq, double* c, double* sn) {
-  const double d = aqq - app;
-  const double a2 = 2.0 * apq;
-  const double tt = (d >= 0.0 ? a2 : -a2) / (fabs(d) + sqrt(d * d + a2 * a2));
-  *c = rsqrt(1.0 + tt * tt);
+// h2 = d^2 + 4 a_pq^2, rounded as the caller forms it.
+__device__ inline void jacobi_cs_of(double d, double a2, double h2, double* c, double* sn) {
+  const double tt = (d >= 0.0 ? a2 : -a2) / (fabs(d) + sqrt(h2));
+  *c = rsqrt(fma(tt, tt, 1.0));
   *sn = tt * *c;
 }
-
-__device__ inline void jacobi_rot(const double* A, int k, int p, int q, double* c, double* sn) {
-  *c = 1.0;
-  *sn = 0.0;
-  if (q >= k) return;  // the dummy player of an odd k
-  const double apq = A[p * k + q];
-  if (apq == 0.0) return;
-  jacobi_cs(A[p * k + p], A[q * k + q], apq, c, sn);
+__device__ inline void jacobi_cs(double app, double aqq, double apq, double* c, double* sn) {
+  const double d = aqq - app, a2 = 2.0 * apq;
+  jacobi_cs_of(d, a2, fma(d, d, a2 * a2), c, sn);
 }
 
-__global__ __launch_bounds__(256) void k_sym_eig(double* T, int k, double* evec, double* evals) {
-  __shared__ double Ab[2][kMaxSketch * kMaxSketch];
-  __shared__ double Vv[kMaxSketch * kMaxSketch];
-  __shared__ double cs_c[kMaxSketch / 2], cs_s[kMaxSketch / 2];
-  __shared__ int pp[kMaxSketch / 2], qq[kMaxSketch / 2];
+// NB blocks a thread (half^2 <= 256 NB).  With an odd k the last player is a dummy: its row and column
+// of A are zeros, which no rotation touches.
+constexpr int kEigLd = kMaxSketch + 1;  // odd: a column's entries fall into different banks
+template <int NB>
+__global__ __launch_bounds__(256) void k_sym_eig(const double* __restrict__ T, int k, int p, double* __restrict__ theta,
+                                                 double* __restrict__ sel) {
+  constexpr int LD = kEigLd;
+  __shared__ double Ab[2][kMaxSketch * LD];
+  __shared__ double Vv[kMaxSketch * LD];
   __shared__ double red[2][4];
+  __shared__ int order[kMaxSketch];
   const int t = threadIdx.x;
-  const int ke = k + (k & 1);  // even number of players; index k (if odd) is a dummy
+  const int ke = k + (k & 1);  // even number of players
   const int half = ke / 2;
-  for (int e = t; e < k * k; e += blockDim.x) {
-    Ab[0][e] = 0.5 * (T[e] + T[(e % k) * k + e / k]);
-    Vv[e] = (e / k == e % k) ? 1.0 : 0.0;
+  for (int e = t; e < ke * ke; e += 256) {
+    const int i = e / ke, j = e % ke;
+    const bool in = i < k && j < k;
+    Ab[0][i * LD + j] = in ? 0.5 * (T[i * k + j] + T[j * k + i]) : 0.0;
+    Vv[i * LD + j] = i == j ? 1.0 : 0.0;
   }
+  // the players of this thread's pairs: slot 0 holds player 0, slots 1..ke-1 the others, one place on
+  // at each step; pair i holds slots i and ke-1-i (after a sweep's ke-1 steps all are back)
+  int xa[NB], xb[NB], ya[NB], yb[NB], vrow[NB];
+  bool own[NB];
+#pragma unroll
+  for (int n = 0; n < NB; ++n) {
+    const int w = t + 256 * n, i1 = w / half, i2 = w % half;
+    own[n] = w < half * half;
+    xa[n] = own[n] ? i1 : 0;
+    xb[n] = own[n] ? ke - 1 - i1 : 1;
+    ya[n] = i2;
+    yb[n] = ke - 1 - i2;
+    vrow[n] = own[n] ? 2 * i1 * LD : 0;
+  }
+  auto next = [ke](int x) { return x == 0 ? 0 : (x + 1 == ke ? 1 : x + 1); };
   __syncthreads();
-  int cur = 0;
+  double* Ac = Ab[0];
+  double* An = Ab[1];
   for (int sweep = 0; sweep < 40; ++sweep) {
-    const double* A = Ab[cur];
     double off = 0.0, dia = 0.0;
-    for (int e = t; e < k * k; e += blockDim.x) {
-      const double v = A[e] * A[e];
-      if (e / k == e % k) dia += v;
+    for (int e = t; e < k * k; e += 256) {
+      const int i = e / k, j = e % k;
+      const double x = Ac[i * LD + j], v = x * x;
+      if (i == j) dia += v;
       else off += v;
     }
     for (int o = 32; o > 0; o >>= 1) {
@@ -257,77 +290,63 @@ __global__ __launch_bounds__(256) void k_sym_eig(double* T, int k, double* evec,
     // relative off-diagonal norm 1e-14 (FP64 Ritz vectors)
     if (toff <= 1e-28 * tdia) break;
     for (int step = 0; step < ke - 1; ++step) {
-      const double* Ac = Ab[cur];
-      double* An = Ab[cur ^ 1];
-      if (t < half) {
-        int p, q;
-        jacobi_player(0, step, ke, k, &p, &q, t);
-        double c, sn;
-        jacobi_rot(Ac, k, p, q, &c, &sn);
-        pp[t] = p;
-        qq[t] = q;
-        cs_c[t] = c;
-        cs_s[t] = sn;
+#pragma unroll
+      for (int n = 0; n < NB; ++n) {
+        if (own[n]) {
+          const int p1 = min(xa[n], xb[n]), q1 = max(xa[n], xb[n]);
+          const int p2 = min(ya[n], yb[n]), q2 = max(ya[n], yb[n]);
+          const int P1 = p1 * LD, Q1 = q1 * LD, P2 = p2 * LD, Q2 = q2 * LD;
+          const double d1p = Ac[P1 + p1], d1q = Ac[Q1 + q1], o1 = Ac[P1 + q1];
+          const double d2p = Ac[P2 + p2], d2q = Ac[Q2 + q2], o2 = Ac[P2 + q2];
+          const double app = Ac[P1 + p2], apq = Ac[P1 + q2], aqp = Ac[Q1 + p2], aqq = Ac[Q1 + q2];
+          // the block's two rows of V, in the columns of its second pair
+          double* vp = Vv + vrow[n] + p2;
+          double* vq = Vv + vrow[n] + q2;
+          const double vp0 = vp[0], vq0 = vq[0], vp1 = vp[LD], vq1 = vq[LD];
+          // both rotations without a branch, so that their chains run side by side
+          const double e1 = d1q - d1p, e2 = d2q - d2p, f1 = 2.0 * o1, f2 = 2.0 * o2;
+          double c1, s1, c2, s2;
+          jacobi_cs_of(e1, f1, fma(f1, f1, e1 * e1), &c1, &s1);
+          jacobi_cs_of(e2, f2, fma(f2, f2, e2 * e2), &c2, &s2);
+          c1 = o1 == 0.0 ? 1.0 : c1;
+          s1 = o1 == 0.0 ? 0.0 : s1;
+          c2 = o2 == 0.0 ? 1.0 : c2;
+          s2 = o2 == 0.0 ? 0.0 : s2;
+          // rows: [p1; q1] <- [c1 -s1; s1 c1] [p1; q1], then columns likewise with (c2, s2)
+          const double xp = fma(c1, app, -(s1 * aqp)), xq = fma(s1, app, c1 * aqp);  // column p2
+          const double yp = fma(c1, apq, -(s1 * aqq)), yq = fma(s1, apq, c1 * aqq);  // column q2
+          An[P1 + p2] = fma(c2, xp, -(s2 * yp));
+          An[P1 + q2] = fma(s2, xp, c2 * yp);
+          An[Q1 + p2] = fma(c2, xq, -(s2 * yq));
+          An[Q1 + q2] = fma(s2, xq, c2 * yq);
+          vp[0] = fma(c2, vp0, -(s2 * vq0));
+          vq[0] = fma(s2, vp0, c2 * vq0);
+          vp[LD] = fma(c2, vp1, -(s2 * vq1));
+          vq[LD] = fma(s2, vp1, c2 * vq1);
+        }
+        xa[n] = next(xa[n]);
+        xb[n] = next(xb[n]);
+        ya[n] = next(ya[n]);
+        yb[n] = next(yb[n]);
       }
       __syncthreads();
-      // 2 x 2 blocks of J^T A J: pairs (i1, i2), one block per thread
-      for (int w = t; w < half * half; w += blockDim.x) {
-        const int i1 = w / half, i2 = w % half;
-        const int p1 = pp[i1], q1 = qq[i1], p2 = pp[i2], q2 = qq[i2];
-        const double c1 = cs_c[i1], s1 = cs_s[i1], c2 = cs_c[i2], s2 = cs_s[i2];
-        const bool r1 = q1 < k, r2 = q2 < k;  // a dummy index has no row or column
-        const double app = Ac[p1 * k + p2];
-        const double apq = r2 ? Ac[p1 * k + q2] : 0.0;
-        const double aqp = r1 ? Ac[q1 * k + p2] : 0.0;
-        const double aqq = (r1 && r2) ? Ac[q1 * k + q2] : 0.0;
-        // rows: [p1; q1] <- [c1 -s1; s1 c1] [p1; q1], then columns likewise with (c2, s2)
-        const double xp = c1 * app - s1 * aqp, xq = s1 * app + c1 * aqp;  // column p2
-        const double yp = c1 * apq - s1 * aqq, yq = s1 * apq + c1 * aqq;  // column q2
-        An[p1 * k + p2] = c2 * xp - s2 * yp;
-        if (r2) An[p1 * k + q2] = s2 * xp + c2 * yp;
-        if (r1) An[q1 * k + p2] = c2 * xq - s2 * yq;
-        if (r1 && r2) An[q1 * k + q2] = s2 * xq + c2 * yq;
-      }
-      // eigenvector columns p, q of every pair: row j, pair i, one owner each
-      for (int w = t; w < half * k; w += blockDim.x) {
-        const int i = w / k, j = w % k;
-        const double sn = cs_s[i];
-        if (sn == 0.0) continue;
-        const int pq = pp[i], q2 = qq[i];
-        const double c = cs_c[i];
-        const double vp = Vv[j * k + pq], vq = Vv[j * k + q2];
-        Vv[j * k + pq] = c * vp - sn * vq;
-        Vv[j * k + q2] = sn * vp + c * vq;
-      }
-      __syncthreads();
-      cur ^= 1;
+      double* x = Ac;
+      Ac = An;
+      An = x;
     }
   }
-  const double* A = Ab[cur];
-  for (int e = t; e < k * k; e += blockDim.x) evec[e] = Vv[e];
-  for (int j = t; j < k; j += blockDim.x) evals[j] = A[j * k + j];
-}
-
-// Select the p largest eigenvalues: theta[j], and the selection/rotation matrix
-// sel (k x p, row-major) whose column j is the eigenvector of the j-th largest.  Lane i finds
-// the rank of eigenvalue i (descending; ties by index, as a stable sort orders them).
-__global__ void k_lmp_finish(const double* evals, const double* evec, int k, int p, double* theta, double* sel) {
-  __shared__ int order[kMaxSketch];
-  __shared__ double ev[kMaxSketch];
-  const int t = threadIdx.x;
-  if (t < k) ev[t] = evals[t];
-  __syncthreads();
   if (t < k) {
+    const double ev = Ac[t * LD + t];
     int rank = 0;
-    for (int i = 0; i < k; ++i) rank += (ev[i] > ev[t]) || (ev[i] == ev[t] && i < t);
+    for (int i = 0; i < k; ++i) {
+      const double o = Ac[i * LD + i];
+      rank += (o > ev) || (o == ev && i < t);
+    }
     order[rank] = t;
+    if (rank < p) theta[rank] = ev;
   }
   __syncthreads();
-  if (t < p) theta[t] = ev[order[t]];
-  for (int e = t; e < k * p; e += blockDim.x) {
-    const int a = e / p, j = e % p;
-    sel[a * p + j] = evec[a * k + order[j]];
-  }
+  for (int e = t; e < k * p; e += 256) sel[e] = Vv[(e / p) * LD + order[e % p]];
 }
 
 // G = X^T Y (row-major k x k, k = k1 + k2 <= 16) over m rows on an NT-thread workgroup by FP64
@@ -410,6 +429,12 @@ __global__ __launch_bounds__(256) void k_gram_small(Strided A, Strided B, int64_
   gram_mfma<256>(A, B, m, k, part, G);
 }
 
+// A^T A, A^T B and B^T B at once, a workgroup each, into G, G + k k and G + 2 k k.
+__global__ __launch_bounds__(256) void k_gram_small3(Strided A, Strided B, int64_t m, int k, double* __restrict__ G) {
+  __shared__ double part[2 * 256];
+  gram_mfma<256>(blockIdx.x == 2 ? B : A, blockIdx.x == 0 ? A : B, m, k, part, G + (int64_t)blockIdx.x * k * k);
+}
+
 // ----------------------------------------------------------- small bases on one workgroup
 // With at most 8 sketch columns (p + oversample) the setup's small dense steps run as two
 // launches: Cholesky-QR twice of Y = S Omega, then the Rayleigh quotient T = Qb^T (S Qb), its
@@ -422,6 +447,52 @@ __device__ inline double small_readlane(double v, int l) {
   const int lo = __builtin_amdgcn_readlane((int)(b & 0xffffffffll), l);
   const int hi = __builtin_amdgcn_readlane((int)(b >> 32), l);
   return __builtin_bit_cast(double, ((long long)hi << 32) | (unsigned)lo);
+}
+
+constexpr int kCholRegs = 20;  // the default sketch; wider ones outgrow the unrolled code
+// k_chol_inv for k <= K with the columns in registers: what another lane holds comes by readlane
+// instead of a round trip through LDS per step (k = 20: 31 us, now 12.5).  Entries below R's
+// diagonal hold leftovers that nothing reads.
+template <int K>
+__global__ __launch_bounds__(64) void k_chol_inv_regs(double* G, int k, int32_t* flags) {
+  static_assert(K <= 64, "a column a lane");
+  const int t = threadIdx.x;
+  double r[K], x[K];
+#pragma unroll
+  for (int a = 0; a < K; ++a) r[a] = a < k && t < k ? G[a * k + t] : 0.0;
+  double gmax = 0.0;
+#pragma unroll
+  for (int a = 0; a < K; ++a)
+    if (a < k) gmax = fmax(gmax, small_readlane(r[a], a));
+  bool bad = false;
+#pragma unroll
+  for (int j = 0; j < K; ++j) {
+    if (j < k) {
+      const double d = small_readlane(r[j], j);
+      if (!isfinite(d)) bad = true;
+      const double rjj = (d > kCholDrop * gmax) ? sqrt(d) : 0.0;
+      const double q = rjj > 0.0 ? r[j] / rjj : 0.0;
+      r[j] = t == j ? rjj : q;
+#pragma unroll
+      for (int a = j + 1; a < K; ++a) r[a] = fma(-small_readlane(q, a), q, r[a]);
+    }
+  }
+#pragma unroll
+  for (int a = K - 1; a >= 0; --a) {
+    x[a] = 0.0;
+    if (a < k) {
+      const double raa = small_readlane(r[a], a);
+      double s = a == t ? 1.0 : 0.0;
+#pragma unroll
+      for (int b = a + 1; b < K; ++b)
+        if (b < k) s = fma(-small_readlane(r[a], b), x[b], s);
+      x[a] = (a <= t && raa > 0.0) ? s / raa : 0.0;
+    }
+  }
+#pragma unroll
+  for (int a = 0; a < K; ++a)
+    if (a < k && t < k) G[a * k + t] = x[a];
+  if (t == 0 && bad) atomicOr(flags, kFlagNumeric);
 }
 
 // Lane src's value of a double, for each lane (ds_bpermute on both halves).
@@ -633,9 +704,16 @@ __global__ __launch_bounds__(kSmallNT) void k_ritz_small(const double* __restric
         const double cpq = lane_shfl(a, p2 * K + q2);
         const double arj = lane_shfl(a, pi * K + j), aic = lane_shfl(a, i * K + pj);
         const double arc = lane_shfl(a, pi * K + pj), vc = lane_shfl(v, i * K + pj);
-        double c1 = 1.0, s1 = 0.0, c2 = 1.0, s2 = 0.0;
-        if (q1 < k && q1 != p1 && rpq != 0.0) jacobi_cs(rpp, rqq, rpq, &c1, &s1);
-        if (q2 < k && q2 != p2 && cpq != 0.0) jacobi_cs(cpp, cqq, cpq, &c2, &s2);
+        // both rotations without a branch, so that their chains of square root, division and
+        // reciprocal root can run side by side
+        double c1, s1, c2, s2;
+        jacobi_cs(rpp, rqq, rpq, &c1, &s1);
+        jacobi_cs(cpp, cqq, cpq, &c2, &s2);
+        const bool n1 = !(q1 < k && q1 != p1 && rpq != 0.0), n2 = !(q2 < k && q2 != p2 && cpq != 0.0);
+        c1 = n1 ? 1.0 : c1;
+        s1 = n1 ? 0.0 : s1;
+        c2 = n2 ? 1.0 : c2;
+        s2 = n2 ? 0.0 : s2;
         // rows [p; q] <- [c -s; s c] [p; q] (entries j and pj of row i), then columns likewise;
         // V <- V J
         const double b = i <= pi ? c1 * a - s1 * arj : s1 * arj + c1 * a;
@@ -745,30 +823,39 @@ hipError_t launch_gram(Strided A, Strided B, int64_t m, int k, double* G, double
   return hipGetLastError();
 }
 
+hipError_t launch_gram_pair(Strided A, Strided B, int64_t m, int k, double* G, double* scratch, hipStream_t st) {
+  if (k < 1 || k > kMaxSketch || m < 1) return hipErrorInvalidValue;
+  if (k <= 16 && m <= 8192) {
+    hipLaunchKernelGGL(k_gram_small3, dim3(3), dim3(256), 0, st, A, B, m, k, G);
+    return hipGetLastError();
+  }
+  hipError_t e = launch_gram(A, A, m, k, G, scratch, st);
+  if (e == hipSuccess) e = launch_gram(A, B, m, k, G + (int64_t)k * k, scratch, st);
+  if (e == hipSuccess) e = launch_gram(B, B, m, k, G + (int64_t)2 * k * k, scratch, st);
+  return e;
+}
+
 hipError_t launch_chol_inv(double* G, int k, int32_t* flags, hipStream_t st) {
   if (k < 1 || k > kMaxSketch) return hipErrorInvalidValue;
-  hipLaunchKernelGGL(k_chol_inv, dim3(1), dim3(64), 0, st, G, k, flags);
+  if (k <= kCholRegs)
+    hipLaunchKernelGGL(k_chol_inv_regs<kCholRegs>, dim3(1), dim3(64), 0, st, G, k, flags);
+  else
+    hipLaunchKernelGGL(k_chol_inv, dim3(1), dim3(64), 0, st, G, k, flags);
   return hipGetLastError();
 }
 
 hipError_t launch_right_mult(Strided A, int64_t m, int k, const double* M, int kout, double* out, int64_t ors,
-                             int64_t ocs, hipStream_t st) {
+                             int64_t ocs, hipStream_t st, const Strided* A2, double* out2) {
   const int64_t cnt = m * kout;
-  hipLaunchKernelGGL(k_right_mult, dim3((unsigned)((cnt + 255) / 256)), dim3(256), 0, st, A, m, k, M, kout, out, ors,
-                     ocs);
+  hipLaunchKernelGGL(k_right_mult, dim3((unsigned)((cnt + 255) / 256), A2 ? 2 : 1), dim3(256), 0, st, A, A2 ? *A2 : A,
+                     m, k, M, kout, out, out2, ors, ocs);
   return hipGetLastError();
 }
 
-hipError_t launch_sym_eig(double* T, int k, double* evec, double* evals, hipStream_t st) {
-  if (k < 1 || k > kMaxSketch) return hipErrorInvalidValue;
-  hipLaunchKernelGGL(k_sym_eig, dim3(1), dim3(256), 0, st, T, k, evec, evals);
-  return hipGetLastError();
-}
-
-hipError_t launch_lmp_finish(const double* evals, const double* evec, int k, int p, double* theta, double* sel,
-                             hipStream_t st) {
+hipError_t launch_sym_eig(const double* T, int k, int p, double* theta, double* sel, hipStream_t st) {
   if (k < 1 || k > kMaxSketch || p > k) return hipErrorInvalidValue;
-  hipLaunchKernelGGL(k_lmp_finish, dim3(1), dim3(64), 0, st, evals, evec, k, p, theta, sel);
+  if (k <= 32) hipLaunchKernelGGL(k_sym_eig<1>, dim3(1), dim3(256), 0, st, T, k, p, theta, sel);
+  else hipLaunchKernelGGL(k_sym_eig<3>, dim3(1), dim3(256), 0, st, T, k, p, theta, sel);
   return hipGetLastError();
 }
 
