@@ -82,6 +82,8 @@ __host__ __device__ constexpr bool tail_lds_sums(int Wn, int NT, int RPT) {
 __host__ __device__ constexpr bool tail_merged(int P, int NT, int RPT) {
   return P <= 4 && tail_lds_sums(4 * P + 4, NT, RPT);
 }
+// Leading dimension of a Ritz basis in LDS.
+__host__ __device__ constexpr int tail_basis_ld(int64_t m) { return (int)((m + 1) & ~(int64_t)1); }
 // Doubles a thread writes for the LDS sums (0: the sums go through wavefront partials).
 __host__ __device__ constexpr int tail_sum_words(int P, int NT, int RPT) {
   return tail_merged(P, NT, RPT) ? 4 * P + 4 : (tail_lds_sums(2 * P + 1, NT, RPT) ? 2 * P + 1 : 0);
@@ -180,16 +182,10 @@ __device__ inline float4 tail_ld16f(__amdgpu_buffer_rsrc_t rs, uint32_t voff, ui
 // even width), so both rows read one window of the direction and the compiler loads each LDS word
 // once for the two.
 
+// (RPT: the rows the wavefront applies, one pair or two.)
 template <int RPT, int NT, int CH, bool ADJ>
 __device__ inline void tail_apply_rows(__amdgpu_buffer_rsrc_t rsA, uint32_t colA, const uint32_t* roff,
-                                       const int* corner, const double* sp, int hh, int ww, int Wp, int64_t m,
-                                       double* qv) {
-  // with two row pairs a thread, pairs whose whole wavefront lies past m are skipped (a uniform
-  // branch; with one pair every wavefront has rows)
-  bool live[RPT / 2];
-#pragma unroll
-  for (int jj = 0; jj < RPT / 2; ++jj)
-    live[jj] = RPT <= 2 || 2 * ((int64_t)(threadIdx.x & ~63) + (int64_t)NT * jj) < m;
+                                       const int* corner, const double* sp, int hh, int ww, int Wp, double* qv) {
 #pragma unroll
   for (int j = 0; j < RPT; ++j) qv[j] = 0.0;
   for (int li = 0; li < hh; ++li) {
@@ -200,13 +196,10 @@ __device__ inline void tail_apply_rows(__amdgpu_buffer_rsrc_t rsA, uint32_t colA
       double2 bv[RPT / 2][CH];
 #pragma unroll
       for (int jj = 0; jj < RPT / 2; ++jj)
-        if (live[jj]) {
 #pragma unroll
-          for (int k = 0; k < CH; ++k) bv[jj][k] = tail_ld16(rsA, roff[jj], so + (uint32_t)k * colA);
-        }
+        for (int k = 0; k < CH; ++k) bv[jj][k] = tail_ld16(rsA, roff[jj], so + (uint32_t)k * colA);
 #pragma unroll
       for (int jj = 0; jj < RPT / 2; ++jj) {
-        if (!live[jj]) continue;
         const double* p0 = sp + corner[2 * jj] + lrow + d0;
         if constexpr (ADJ) {
           // the pair's shared window (CH + 1 entries from an even index) in 16-byte LDS reads
@@ -239,13 +232,10 @@ __device__ inline void tail_apply_rows(__amdgpu_buffer_rsrc_t rsA, uint32_t colA
       double2 bv[RPT / 2][CH];
 #pragma unroll
       for (int jj = 0; jj < RPT / 2; ++jj)
-        if (live[jj]) {
 #pragma unroll
-          for (int k = 0; k < CH; ++k) bv[jj][k] = tail_ld16(rsA, roff[jj], so + (uint32_t)min(k, last) * colA);
-        }
+        for (int k = 0; k < CH; ++k) bv[jj][k] = tail_ld16(rsA, roff[jj], so + (uint32_t)min(k, last) * colA);
 #pragma unroll
       for (int jj = 0; jj < RPT / 2; ++jj) {
-        if (!live[jj]) continue;
         const double* p0 = sp + corner[2 * jj] + lrow + d0;
         const double* p1 = ADJ ? p0 + 1 : sp + corner[2 * jj + 1] + lrow + d0;
 #pragma unroll
@@ -267,16 +257,13 @@ __device__ inline void tail_apply_rows(__amdgpu_buffer_rsrc_t rsA, uint32_t colA
 // column of quads; rowq: a row's byte offset in it).  The direction past a stencil row's last
 // entry holds finite values (the next lattice row, or the zeroed slack after the padded lattice),
 // which the zero weights cancel.  CH entries a chunk (a multiple of 4); the sums are in FP64.
-template <int RPT, int NT, int CH, bool ADJ>
+// CHAIN: the last quads join the chain of the sums; otherwise each is summed apart and added.
+template <int RPT, int NT, int CH, bool ADJ, bool CHAIN>
 __device__ inline void tail_apply_rows_q(__amdgpu_buffer_rsrc_t rsQ, uint32_t colQ, const uint32_t* rowq,
-                                         const int* corner, const double* sp, int hh, int ww4, int Wp, int64_t m,
+                                         const int* corner, const double* sp, int hh, int ww4, int Wp,
                                          double* qv) {
   static_assert(CH % 4 == 0, "whole quads");
   constexpr int CQ = CH / 4;
-  bool live[RPT / 2];
-#pragma unroll
-  for (int jj = 0; jj < RPT / 2; ++jj)
-    live[jj] = RPT <= 2 || 2 * ((int64_t)(threadIdx.x & ~63) + (int64_t)NT * jj) < m;
 #pragma unroll
   for (int j = 0; j < RPT; ++j) qv[j] = 0.0;
   for (int li = 0; li < hh; ++li) {
@@ -287,10 +274,8 @@ __device__ inline void tail_apply_rows_q(__amdgpu_buffer_rsrc_t rsQ, uint32_t co
       float4 bv[RPT][CQ];
 #pragma unroll
       for (int j = 0; j < RPT; ++j)
-        if (live[j / 2]) {
 #pragma unroll
-          for (int q = 0; q < CQ; ++q) bv[j][q] = tail_ld16f(rsQ, rowq[j], so + (uint32_t)q * colQ);
-        }
+        for (int q = 0; q < CQ; ++q) bv[j][q] = tail_ld16f(rsQ, rowq[j], so + (uint32_t)q * colQ);
       // every load of the chunk goes out before the first is used (widening each one as it lands
       // lets the compiler reuse its registers and wait for every load in turn)
       __builtin_amdgcn_sched_barrier(0);
@@ -298,8 +283,7 @@ __device__ inline void tail_apply_rows_q(__amdgpu_buffer_rsrc_t rsQ, uint32_t co
         // the pair's shared window (CH + 1 entries from an even index) in 16-byte LDS reads
 #pragma unroll
         for (int jj = 0; jj < RPT / 2; ++jj) {
-          if (!live[jj]) continue;
-          const double* pw = sp + corner[2 * jj] + lrow + d0;
+            const double* pw = sp + corner[2 * jj] + lrow + d0;
           double w[CH + 1];
 #pragma unroll
           for (int i = 0; i < CH / 2; ++i) {
@@ -323,7 +307,6 @@ __device__ inline void tail_apply_rows_q(__amdgpu_buffer_rsrc_t rsQ, uint32_t co
       } else {
 #pragma unroll
         for (int j = 0; j < RPT; ++j) {
-          if (!live[j / 2]) continue;
           const double* pj = sp + corner[j] + lrow + d0;
 #pragma unroll
           for (int q = 0; q < CQ; ++q) {
@@ -342,19 +325,23 @@ __device__ inline void tail_apply_rows_q(__amdgpu_buffer_rsrc_t rsQ, uint32_t co
       float4 bv[RPT][CQ];
 #pragma unroll
       for (int j = 0; j < RPT; ++j)
-        if (live[j / 2]) {
 #pragma unroll
-          for (int q = 0; q < CQ; ++q)
-            bv[j][q] = tail_ld16f(rsQ, rowq[j], so + (uint32_t)min(q, lastq) * colQ);
-        }
+        for (int q = 0; q < CQ; ++q) bv[j][q] = tail_ld16f(rsQ, rowq[j], so + (uint32_t)min(q, lastq) * colQ);
       __builtin_amdgcn_sched_barrier(0);
 #pragma unroll
       for (int j = 0; j < RPT; ++j) {
-        if (!live[j / 2]) continue;
         const double* pj = (ADJ && (j & 1)) ? sp + corner[j - 1] + lrow + d0 + 1 : sp + corner[j] + lrow + d0;
 #pragma unroll
         for (int q = 0; q < CQ; ++q) {
           const int qq = 4 * min(q, lastq);
+          if constexpr (CHAIN) {
+            double c = qv[j] + (double)bv[j][q].x * pj[qq];
+            c += (double)bv[j][q].y * pj[qq + 1];
+            c += (double)bv[j][q].z * pj[qq + 2];
+            c += (double)bv[j][q].w * pj[qq + 3];
+            qv[j] = q <= lastq ? c : qv[j];
+            continue;
+          }
           const double t = (double)bv[j][q].x * pj[qq] + (double)bv[j][q].y * pj[qq + 1] +
                            (double)bv[j][q].z * pj[qq + 2] + (double)bv[j][q].w * pj[qq + 3];
           qv[j] += q <= lastq ? t : 0.0;
@@ -421,12 +408,19 @@ __global__ __launch_bounds__(NT) void k_pcg_tail(TailInst one, const TailInst* _
   constexpr int CH = RPT >= 4 ? 4 : 8;
   constexpr int CHQ = 8;
   // the Ritz vectors of the thread's rows stay in registers when they fit
+  constexpr bool kLow = sizeof(BT) == 4;
   constexpr bool kCache = tail_caches_ritz(P, RPT, NT);
   constexpr bool kLdsSums = tail_lds_sums(2 * P + 1, NT, RPT);
   constexpr bool kMerged = tail_merged(P, NT, RPT);
   constexpr int WM = 4 * P + 4;
   constexpr int kC = kCache ? RPT * P : 1;
-  constexpr bool kLow = sizeof(BT) == 4;
+  // else, where an iteration outside its apply has the registers, its dots keep them for its
+  // preconditioned residual, and a pair of rows comes in 16 bytes (an iteration of
+  // k_pcg_tail<4, 4, 512, float> at m about 1600: 24.5 k cycles, 21.5 k so; dots and residual 5.6 k
+  // and 1.5 k of them)
+  constexpr bool kKeep = !kCache && P > 0 && RPT * P <= 16 && NT < 1024;
+  constexpr int kK = kKeep ? RPT * P : 1;
+  constexpr bool kKeepPhi = !MULTI && !kLow;  // the others would spill: Phi is read again (from LDS)
   __shared__ double sred1[1][NW];
   __shared__ double sredW[W][NW];
   __shared__ double sG[3 * P * P + P + 1];
@@ -446,7 +440,7 @@ __global__ __launch_bounds__(NT) void k_pcg_tail(TailInst one, const TailInst* _
   int64_t m = 0;
   bool band = true;
   Grid g{};
-  int Wp = 0, npad = 0, nh = 0, hh = 1, ww = 1, phi_lds = 0;
+  int Wp = 0, npad = 0, nh = 0, hh = 1, ww = 1, phi_lds = 0, ldf = 0;
   bool adj = false;  // every row pair's stencils are one entry apart
   // the wrapped copies of a row's direction entry are written with it (no halo pass) where each
   // periodic axis is at least twice its stencil reach: then an entry has at most 3 copies
@@ -500,13 +494,15 @@ __global__ __launch_bounds__(NT) void k_pcg_tail(TailInst one, const TailInst* _
       colF = (uint32_t)(lmp.ld * 8);
       // rows of partial sums (tail_part_stride apart), then Phi (P x m), when phi_lds
       part = sp + npad + kTailSlack;
-      sF = part + tail_sum_words(P, NT, RPT) * tail_part_stride(tail_part_rows(NT, RPT));
-      sH = sF + (int64_t)P * m;             // S Phi (P x m)
+      // (even leading dimension and offset: a row pair in 16 bytes)
+      ldf = tail_basis_ld(m);
+      sF = sp + ((npad + kTailSlack + tail_sum_words(P, NT, RPT) * tail_part_stride(tail_part_rows(NT, RPT)) + 1) & ~1);
+      sH = sF + P * ldf;                    // S Phi (P x m)
       if (phi_lds) {  // 1: Phi only, 2: Phi and S Phi
         for (int o = tid; o < P * (int)m; o += NT) {
           const int l = o / (int)m, r = o % (int)m;
-          sF[o] = tail_ld8(rsF, (uint32_t)r * 8, l * colF);
-          if (phi_lds == 2) sH[o] = tail_ld8(rsG, (uint32_t)r * 8, l * colF);
+          sF[l * ldf + r] = tail_ld8(rsF, (uint32_t)r * 8, l * colF);
+          if (phi_lds == 2) sH[l * ldf + r] = tail_ld8(rsG, (uint32_t)r * 8, l * colF);
         }
       }
 #pragma unroll
@@ -597,14 +593,26 @@ __global__ __launch_bounds__(NT) void k_pcg_tail(TailInst one, const TailInst* _
         }
         __syncthreads();
       }
-      if (!kLow || fp64) {
-        if (adj) tail_apply_rows<RPT, NT, CH, true>(rsA, colA, roff, corner, sp, hh, ww, Wp, m, qv);
-        else tail_apply_rows<RPT, NT, CH, false>(rsA, colA, roff, corner, sp, hh, ww, Wp, m, qv);
-      } else {
-        const int ww4 = (ww + 3) & ~3;
-        if (adj) tail_apply_rows_q<RPT, NT, CHQ, true>(rsI, colI, roffI, corner, sp, hh, ww4, Wp, m, qv);
-        else tail_apply_rows_q<RPT, NT, CHQ, false>(rsI, colI, roffI, corner, sp, hh, ww4, Wp, m, qv);
-      }
+      // pairs from the LP-th on, whose whole wavefront lies past m, are skipped (one branch for the
+      // whole product: a branch around each pair's loads kept a chunk's from going out together, the
+      // FP64 product of 8 x 480 points 10.3 k cycles for 7.9 k)
+      auto rows = [&](auto lp) {
+        constexpr int R = 2 * lp.value;
+#pragma unroll
+        for (int jj = R; jj < RPT; ++jj) qv[jj] = 0.0;
+        if (!kLow || fp64) {
+          if (adj) tail_apply_rows<R, NT, CH, true>(rsA, colA, roff, corner, sp, hh, ww, Wp, qv);
+          else tail_apply_rows<R, NT, CH, false>(rsA, colA, roff, corner, sp, hh, ww, Wp, qv);
+        } else {
+          const int ww4 = (ww + 3) & ~3;
+          if (adj) tail_apply_rows_q<R, NT, CHQ, true, (RPT > 2)>(rsI, colI, roffI, corner, sp, hh, ww4, Wp, qv);
+          else tail_apply_rows_q<R, NT, CHQ, false, (RPT > 2)>(rsI, colI, roffI, corner, sp, hh, ww4, Wp, qv);
+        }
+      };
+      static_assert(RPT <= 4, "at most two pairs a thread");
+      const bool full = RPT == 2 || 2 * (__builtin_amdgcn_readfirstlane(tid) + NT) < (int)m;
+      if (full) rows(std::integral_constant<int, RPT / 2>{});
+      else rows(std::integral_constant<int, 1>{});
 #pragma unroll
       for (int jj = 0; jj < RPT; ++jj) qv[jj] += sig1 * v[jj];
     };
@@ -669,6 +677,30 @@ __global__ __launch_bounds__(NT) void k_pcg_tail(TailInst one, const TailInst* _
 #pragma unroll
         for (int jj = 0; jj < RPT; ++jj) qv[jj] = 0.0;
       }
+      double ka[kK], kb[kK];
+      // The Ritz vectors of the thread's rows: 16 bytes bring both rows of a pair (those of rows past
+      // m are not used).  The offsets are opaque: seen as the loop's invariants, the loads and their
+      // addresses would move before it, and the apply would spill them.
+      auto load_basis = [&](double* k, const double* lds, __amdgpu_buffer_rsrc_t rs, bool in_lds) {
+#pragma unroll
+        for (int jj = 0; jj < RPT / 2; ++jj) {
+          uint32_t ro = roff[jj];
+          asm volatile("" : "+v"(ro));
+#pragma unroll
+          for (int l = 0; l < P; ++l) {
+            const double2 t = in_lds ? *reinterpret_cast<const double2*>(lds + l * ldf + ro / 8)
+                                     : tail_ld16(rs, ro, l * colF);
+            k[(2 * jj * P + l) % kK] = t.x;
+            k[((2 * jj + 1) * P + l) % kK] = t.y;
+          }
+        }
+      };
+      auto load_phi = [&](double* k) { load_basis(k, sF, rsF, phi_lds != 0); };
+      if (kKeep) {
+        __builtin_amdgcn_sched_barrier(0);
+        load_basis(kb, sH, rsG, phi_lds == 2);
+        load_phi(ka);
+      }
       // sums: 0 p^T q, 1 q^T q, 2 r^T q, 3 r^T r, then Phi^T q, (S Phi)^T q, Phi^T r, (S Phi)^T r
       double acc[WM];
 #pragma unroll
@@ -684,10 +716,12 @@ __global__ __launch_bounds__(NT) void k_pcg_tail(TailInst one, const TailInst* _
           acc[3] += rj * rj;
 #pragma unroll
           for (int l = 0; l < P; ++l) {
-            const double a = kCache ? ph[(jj * P + l) % kC]
-                                    : (phi_lds ? sF[l * m + r] : tail_ld8(rsF, (uint32_t)r * 8, l * colF));
-            const double b = kCache ? sph[(jj * P + l) % kC]
-                                    : (phi_lds == 2 ? sH[l * m + r] : tail_ld8(rsG, (uint32_t)r * 8, l * colF));
+            const double a = kCache   ? ph[(jj * P + l) % kC]
+                             : kKeep ? ka[(jj * P + l) % kK]
+                                    : (phi_lds ? sF[l * ldf + r] : tail_ld8(rsF, (uint32_t)r * 8, l * colF));
+            const double b = kCache   ? sph[(jj * P + l) % kC]
+                             : kKeep ? kb[(jj * P + l) % kK]
+                                    : (phi_lds == 2 ? sH[l * ldf + r] : tail_ld8(rsG, (uint32_t)r * 8, l * colF));
             acc[4 + l] += a * qj;
             acc[4 + P + l] += b * qj;
             acc[4 + 2 * P + l] += a * rj;
@@ -763,6 +797,7 @@ __global__ __launch_bounds__(NT) void k_pcg_tail(TailInst one, const TailInst* _
       const double beta = first ? 0.0 : rzn / rz;
       rz = rzn;
       first = false;
+      if (kKeep && !kKeepPhi) load_phi(ka);
 #pragma unroll
       for (int jj = 0; jj < RPT; ++jj) {
         const int64_t r = tail_row<NT>(tid, jj);
@@ -770,10 +805,12 @@ __global__ __launch_bounds__(NT) void k_pcg_tail(TailInst one, const TailInst* _
           double z = rv[jj];
 #pragma unroll
           for (int l = 0; l < P; ++l) {
-            const double a = kCache ? ph[(jj * P + l) % kC]
-                                    : (phi_lds ? sF[l * m + r] : tail_ld8(rsF, (uint32_t)r * 8, l * colF));
-            const double b = kCache ? sph[(jj * P + l) % kC]
-                                    : (phi_lds == 2 ? sH[l * m + r] : tail_ld8(rsG, (uint32_t)r * 8, l * colF));
+            const double a = kCache   ? ph[(jj * P + l) % kC]
+                             : kKeep ? ka[(jj * P + l) % kK]
+                                    : (phi_lds ? sF[l * ldf + r] : tail_ld8(rsF, (uint32_t)r * 8, l * colF));
+            const double b = kCache   ? sph[(jj * P + l) % kC]
+                             : kKeep ? kb[(jj * P + l) % kK]
+                                    : (phi_lds == 2 ? sH[l * ldf + r] : tail_ld8(rsG, (uint32_t)r * 8, l * colF));
             z -= b * c1[l] + a * gm[l];
           }
           pv[jj] = z + beta * pv[jj];
@@ -819,9 +856,9 @@ __global__ __launch_bounds__(NT) void k_pcg_tail(TailInst one, const TailInst* _
 #pragma unroll
           for (int l = 0; l < P; ++l) {
             const double a = kCache ? ph[(jj * P + l) % kC]
-                                    : (phi_lds ? sF[l * m + r] : tail_ld8(rsF, (uint32_t)r * 8, l * colF));
+                                    : (phi_lds ? sF[l * ldf + r] : tail_ld8(rsF, (uint32_t)r * 8, l * colF));
             const double b = kCache ? sph[(jj * P + l) % kC]
-                                    : (phi_lds == 2 ? sH[l * m + r] : tail_ld8(rsG, (uint32_t)r * 8, l * colF));
+                                    : (phi_lds == 2 ? sH[l * ldf + r] : tail_ld8(rsG, (uint32_t)r * 8, l * colF));
             acc[1 + l] += a * rv[jj];
             acc[1 + P + l] += b * rv[jj];
           }
@@ -893,9 +930,9 @@ __global__ __launch_bounds__(NT) void k_pcg_tail(TailInst one, const TailInst* _
 #pragma unroll
           for (int l = 0; l < P; ++l) {
             const double a = kCache ? ph[(jj * P + l) % kC]
-                                    : (phi_lds ? sF[l * m + r] : tail_ld8(rsF, (uint32_t)r * 8, l * colF));
+                                    : (phi_lds ? sF[l * ldf + r] : tail_ld8(rsF, (uint32_t)r * 8, l * colF));
             const double b = kCache ? sph[(jj * P + l) % kC]
-                                    : (phi_lds == 2 ? sH[l * m + r] : tail_ld8(rsG, (uint32_t)r * 8, l * colF));
+                                    : (phi_lds == 2 ? sH[l * ldf + r] : tail_ld8(rsG, (uint32_t)r * 8, l * colF));
             z -= b * scoef[l] + a * scoef[P + l];
           }
           pv[jj] = z + beta * pv[jj];
@@ -1140,7 +1177,8 @@ size_t tail_inst_lds(TailInst& d, size_t stat) {
   size_t lds = tail_lds_bytes(d.ap);
   lds += (size_t)tail_sum_words(P, NT, RPT) * tail_part_stride(tail_part_rows(NT, RPT)) * sizeof(double);
   if (stat + lds > kTailLdsBig) return 0;
-  const size_t one = (size_t)8 * P * d.st.m;  // one basis, FP64
+  lds += sizeof(double);                                // the bases start at an even double
+  const size_t one = (size_t)8 * P * tail_basis_ld(d.st.m);  // one basis, FP64
   d.phi_lds = 0;
   if (P > 0 && !tail_caches_ritz(P, RPT, NT)) {
     if (stat + lds + 2 * one <= kTailLdsBig) d.phi_lds = 2;

@@ -150,6 +150,33 @@ def test_queue_of_many_instances(count):
         assert upd(Xs[j].cpu().numpy(), want) < 1e-6, pr.name
 
 
+@pytest.mark.parametrize("precision", [ie.FP64, ie.MIXED_FP32])
+@pytest.mark.parametrize("m,c", [(1025, 8.0), (1026, 9.0), (1160, 10.0), (1535, 11.0), (1537, 8.5), (2047, 9.5),
+                                 (2048, 10.5)])
+def test_four_rows_a_thread(m, c, precision):
+    """Systems of 1024 < m <= 2048 observations in the persistent kernel, alone and in a batch: odd
+    and even m at the ends of its wavefronts' second pairs, stencils (2 ceil(2 c) - 1 points) of every
+    remainder of a quad and of a chunk of two; against the state-domain FP64 loop, another path
+    altogether, at 1e-6, the FP64-mode bound at rtol 1e-8."""
+    prob = syn.gaussian_problem(4 * m, 4, 24.0, 4 * c, 4, 0.25, 3, 100.0, 41, name="four-%d" % m)
+    say("four rows", m, c, precision)
+    P = ie.Problem.from_synthetic(prob)
+    nodes = ie.quadrature_elliptic(prob.Q, prob.ell)
+    Xr, mr, _, _ = run_single(P, prob, *nodes, ie.default_opts())
+    opts = make_opts("lattice", precision, P, n_ritz=4, oversample=4, tail_systems=100000)
+    Xa, mu, st, sm = run_single(P, prob, *nodes, opts)
+    assert st.converged.all() and sm.converged.all()
+    mean = prob.X.mean(axis=1)
+    assert upd(Xa, Xr) < 1e-6 and upd(mu - mean, mr - mean) < 1e-6
+    runner = ie.BatchedRunner([P, P], [nodes, nodes], opts, ys=[prob.y, prob.y], lattices=[P.lattice()] * 2)
+    assert runner.run() == ie.OK
+    torch.cuda.synchronize()
+    Xs, mus = runner.results()
+    assert runner.one_launch()
+    for j in range(2):
+        assert upd(Xs[j].cpu().numpy(), Xr) < 1e-6 and upd(mus[j].cpu().numpy() - mean, mr - mean) < 1e-6
+
+
 def test_batched_instance_matches_oracle():
     probs = batch()
     Ps = [ie.Problem.from_synthetic(pr) for pr in probs]
