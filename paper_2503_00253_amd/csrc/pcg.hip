@@ -227,7 +227,9 @@ __global__ __launch_bounds__(256) void k_pcg_fused(PCGState st, LMP lmp, int mod
   // The Ritz vectors are read for the dots of r and, when they fit in registers, kept for the
   // preconditioned residual, so each system reads them once per iteration.  (They are not loaded
   // with the system's data: that many loads in flight would stall the first round trip.)
-  constexpr bool kCache = (RPT * P <= 24);
+  // (With the 2 P + 1 sums they have to leave two wavefronts a SIMD: 4096 points, 1024 observations, 10
+  // Ritz pairs 16.5 us a launch with a second read, 14.5 without.)
+  constexpr bool kCache = RPT * P <= 24 || (RPT <= 4 && RPT * P + P <= 50);
   constexpr int kC = (kCache && P > 0) ? RPT * P : 1;
   double ph[kC], sph[kC];
   if (P > 0) {
