@@ -246,8 +246,7 @@ __device__ inline double stencil_value(const Grid& g, int64_t a, int64_t b) {
 // memory took most of the time.  From kDiagTile entries on, tiles of 16 x 16 pairs have their
 // members' dot products formed by the matrix cores (the plain loop is bound by its two LDS reads a
 // multiply-add) and are weighted and summed where they stand.  (100 rows of 177 entries, 20
-// members: 200 us, now 66: the latencies of 36 tiles a wavefront.)
-constexpr int kDiagThreads = 256;
+// members: 200 us, now 32 on sixteen wavefronts a row; 66 on four: the latencies of 36 tiles each.)
 constexpr int kDiagStage = 4096;  // doubles
 constexpr int kDiagRow = 256;     // entries
 constexpr int kDiagTile = 16;
@@ -262,7 +261,8 @@ __device__ inline int32_t wrap_near(int32_t d, int32_t len, int32_t periodic) {
   return t - len / 2;
 }
 
-__global__ __launch_bounds__(kDiagThreads) void k_diag_S(const int32_t* __restrict__ h_ptr,
+template <int NT>
+__global__ __launch_bounds__(NT) void k_diag_S(const int32_t* __restrict__ h_ptr,
                                                          const int32_t* __restrict__ h_idx,
                                                          const double* __restrict__ h_w,
                                                          const double* __restrict__ r_var,
@@ -270,7 +270,7 @@ __global__ __launch_bounds__(kDiagThreads) void k_diag_S(const int32_t* __restri
                                                          Grid g, const double* __restrict__ dense_L,
                                                          double* __restrict__ diagS) {
   __shared__ double zs[kDiagStage];
-  __shared__ double part[kDiagThreads / 64];
+  __shared__ double part[NT / 64];
   __shared__ double sw[kDiagRow];
   __shared__ int32_t sz[kDiagRow], sx[kDiagRow];  // grid row (-1: not a point of the grid) and column
   const int64_t r = blockIdx.x;
@@ -280,7 +280,7 @@ __global__ __launch_bounds__(kDiagThreads) void k_diag_S(const int32_t* __restri
   const bool staged = cnt <= kDiagStage;
   const bool small = cnt <= kDiagRow;
   if (small) {
-    for (int t = tid; t < (int)cnt; t += kDiagThreads) {
+    for (int t = tid; t < (int)cnt; t += NT) {
       const int32_t a = h_idx[e0 + t];
       const bool ok = a >= 0 && a < n;
       sw[t] = h_w[e0 + t];
@@ -296,7 +296,7 @@ __global__ __launch_bounds__(kDiagThreads) void k_diag_S(const int32_t* __restri
       __syncthreads();  // the previous chunk's reads are done
       const int c = (int)max<int64_t>(cnt, 1), count = (int)(cnt * ni);  // at most kDiagStage
 #pragma unroll 4
-      for (int t = tid; t < count; t += kDiagThreads) {
+      for (int t = tid; t < count; t += NT) {
         const int i = t / c, e = t - i * c;
         if (small) {
           const int64_t a = sz[e] < 0 ? -1 : (int64_t)sz[e] * g.nx + sx[e];
@@ -312,7 +312,7 @@ __global__ __launch_bounds__(kDiagThreads) void k_diag_S(const int32_t* __restri
     if (small && cnt >= kDiagTile) {
       const int c = (int)cnt, count = (int)ni, lane = tid & 63, li = lane & 15, kq = lane >> 4;
       const int side = (c + 15) / 16;
-      for (int tile = tid >> 6; tile < side * side; tile += kDiagThreads / 64) {
+      for (int tile = tid >> 6; tile < side * side; tile += NT / 64) {
         const int ec = 16 * (tile / side), fc = 16 * (tile % side);
         // A lane l -> (e l%16, member l/16); B lane l -> (member l/16, f l%16); D register v of
         // lane l -> (e 4v + l/16, f l%16)
@@ -357,8 +357,8 @@ __global__ __launch_bounds__(kDiagThreads) void k_diag_S(const int32_t* __restri
     if (small) {
       const int c = (int)cnt, count = (int)ni;
       int e = c > 0 ? tid / c : 0, f = c > 0 ? tid % c : 0;
-      const int de = c > 0 ? kDiagThreads / c : 0, df = kDiagThreads - de * c;
-      for (int q = tid; q < c * c; q += kDiagThreads) {
+      const int de = c > 0 ? NT / c : 0, df = NT - de * c;
+      for (int q = tid; q < c * c; q += NT) {
         const int32_t za = sz[e], zb = sz[f];
         double l = 0.0;
         if (za >= 0 && zb >= 0) {
@@ -385,7 +385,7 @@ __global__ __launch_bounds__(kDiagThreads) void k_diag_S(const int32_t* __restri
       }
       continue;
     }
-    for (int64_t q = tid; q < cnt * cnt; q += kDiagThreads) {
+    for (int64_t q = tid; q < cnt * cnt; q += NT) {
       const int64_t e = q / cnt, f = q - e * cnt;
       const int64_t a = h_idx[e0 + e], b = h_idx[e0 + f];
       if (a < 0 || a >= n || b < 0 || b >= n) continue;
@@ -405,7 +405,7 @@ __global__ __launch_bounds__(kDiagThreads) void k_diag_S(const int32_t* __restri
   __syncthreads();
   if (tid == 0) {
     double tot = 0.0;
-    for (int w = 0; w < kDiagThreads / 64; ++w) tot += part[w];
+    for (int w = 0; w < NT / 64; ++w) tot += part[w];
     diagS[r] = tot / r_var[r];
   }
 }
@@ -519,8 +519,15 @@ hipError_t launch_diag_S(const int32_t* h_ptr, const int32_t* h_idx, const doubl
                          const double* Z, int64_t n, int64_t N, int64_t m, const Grid& g, const double* dense_L,
                          double* diagS, hipStream_t st) {
   if (m <= 0) return hipSuccess;
-  hipLaunchKernelGGL(k_diag_S, dim3((unsigned)m), dim3(kDiagThreads), 0, st, h_ptr, h_idx, h_w, r_var, Z, n, N, g,
-                     dense_L, diagS);
+  // up to a row a CU, sixteen wavefronts share it; more rows fill the chip by themselves, and the
+  // smaller blocks of point observations start sooner (1024 rows of one entry: 7 us at 256 threads, 10
+  // at 512)
+  if (m <= 256)
+    hipLaunchKernelGGL(k_diag_S<1024>, dim3((unsigned)m), dim3(1024), 0, st, h_ptr, h_idx, h_w, r_var, Z, n, N, g,
+                       dense_L, diagS);
+  else
+    hipLaunchKernelGGL(k_diag_S<256>, dim3((unsigned)m), dim3(256), 0, st, h_ptr, h_idx, h_w, r_var, Z, n, N, g,
+                       dense_L, diagS);
   return hipGetLastError();
 }
 
