@@ -516,9 +516,12 @@ hipError_t launch_innovation(const int32_t* h_ptr, const int32_t* h_idx, const d
 }
 
 hipError_t launch_diag_S(const int32_t* h_ptr, const int32_t* h_idx, const double* h_w, const double* r_var,
-                         const double* Z, int64_t n, int64_t N, int64_t m, const Grid& g, const double* dense_L,
+                         const double* Z, int64_t n, int64_t N, int64_t m, const Grid& grid, const double* dense_L,
                          double* diagS, hipStream_t st) {
   if (m <= 0) return hipSuccess;
+  // an explicit L has no grid: its points are those of one row, so the kernel's divisions are by n
+  const Grid g = dense_L ? Grid{1, (int)n, 0, 0, 0, 0, nullptr, nullptr, nullptr} : grid;
+  if (g.nx < 1 || g.nz < 1) return hipErrorInvalidValue;
   // up to a row a CU, sixteen wavefronts share it; more rows fill the chip by themselves, and the
   // smaller blocks of point observations start sooner (1024 rows of one entry: 7 us at 256 threads, 10
   // at 512)
