@@ -2013,12 +2013,15 @@ int batched_one_launch(const infoesrf_problem* probs, int count, const int32_t* 
     for (int w = 0; w < nw; ++w) IE_HIP(hipStreamWaitEvent(ws[w], e, 0));
     return 0;
   };
-  auto join = [&](int phase) -> int {  // `st` waits for the worker streams
+  auto join = [&](int phase) -> int {  // `st` waits for the worker streams, every one whatever fails
+    hipError_t first = hipSuccess;
     for (int w = 0; w < nw; ++w) {
       const hipEvent_t e = ev.e[phase * (1 + nw) + 1 + w];
-      IE_HIP(hipEventRecord(e, ws[w]));
-      IE_HIP(hipStreamWaitEvent(st, e, 0));
+      hipError_t r = hipEventRecord(e, ws[w]);
+      if (r == hipSuccess) r = hipStreamWaitEvent(st, e, 0);
+      if (first == hipSuccess) first = r;
     }
+    IE_HIP(first);
     return 0;
   };
   IE_TRY(fork(0));
@@ -2047,10 +2050,11 @@ int batched_one_launch(const infoesrf_problem* probs, int count, const int32_t* 
   // has its own stream, so the next one's workgroups take the CUs that the last systems of a
   // class leave idle.
   IE_TRY(fork(1));
+  hipError_t refused = hipSuccess;  // of a class: those launched before it are still joined
   if (nl > 0) {
     int t0 = 0;
     int64_t s0 = 0;
-    for (size_t c = 0; c < classes.size(); ++c) {
+    for (size_t c = 0; c < classes.size() && refused == hipSuccess; ++c) {
       const std::vector<int>& cl = classes[c];
       std::vector<TailInst> ordered(cl.size());
       int64_t segc = 0;
@@ -2061,13 +2065,17 @@ int batched_one_launch(const infoesrf_problem* probs, int count, const int32_t* 
       }
       // the launch writes the table, builds the queue (live systems instance by instance,
       // largest first) and iterates
-      IE_HIP(launch_pcg_tail_multi(ordered.data(), (int)cl.size(), ba.table + t0, ba.seg + s0, ba.cnt + t0,
-                                   ba.list + s0, ba.words + 2 * c, ba.words + 2 * c + 1, segc, ws[c % nw]));
+      refused = launch_pcg_tail_multi(ordered.data(), (int)cl.size(), ba.table + t0, ba.seg + s0, ba.cnt + t0,
+                                      ba.list + s0, ba.words + 2 * c, ba.words + 2 * c + 1, segc, ws[c % nw]);
       t0 += (int)cl.size();
       s0 += segc;
     }
   }
   IE_TRY(join(1));
+  if (refused != hipSuccess) {
+    set_error(std::string("persistent launch of a batch: ") + hipGetErrorString(refused));
+    return INFOESRF_ERR_HIP;
+  }
   // per instance: u_bar_i = sum_q p_q u_{q,i} (and the mean's u as column N), the final updates
   // and the counters: some ten launches of a few us, over the worker streams again (one after the
   // other on `st` they took 0.3 ms of a batch of 8 small filters)

@@ -1,0 +1,62 @@
+"""What infoesrf_update_batched leaves on the caller's stream: its work is ordered there also where one
+class of instances is refused after another was launched.
+"""
+import sys
+
+import numpy as np
+import pytest
+
+import synthetic as syn
+
+pytestmark = pytest.mark.gpu
+
+torch = pytest.importorskip("torch")
+from paper_2503_00253_amd import infoesrf as ie  # noqa: E402
+
+
+def say(*a):
+    print("[case]", *a, file=sys.stderr, flush=True)
+
+
+def runner(probs, Q, **kw):
+    Ps = {id(p): ie.Problem.from_synthetic(p) for p in probs}
+    Ps = [Ps[id(p)] for p in probs]
+    opts = ie.default_opts(host_sync=0, apply_domain=ie.DOMAIN_OBS_LATTICE, **kw)
+    return ie.BatchedRunner(Ps, [ie.quadrature_elliptic(Q, 100.0)] * len(probs), opts, ys=[p.y for p in probs],
+                            lattices=[P.lattice() for P in Ps])
+
+
+def test_a_refused_class_leaves_no_stream_behind():
+    """A class holds at most 2048 instances.  One of 600 observations is launched first, then 2049 small
+    ones are refused on the host: the call fails as a whole, and the first class is joined into the
+    caller's stream all the same.  Under capture that is seen at the capture's end, which takes no stream
+    that has not joined back."""
+    one = syn.gaussian_problem(2400, 4, 20.0, 30.0, 4, 0.25, 2, 100.0, 9, name="first")
+    small = syn.gaussian_problem(32, 2, 4.0, 4.0, 4, 0.25, 2, 100.0, 10, name="small")
+    say("refused class")
+    r = runner([one] + [small] * 2049, 2, n_ritz=0, oversample=0)
+    assert r.one_launch()
+    with pytest.raises(ie.InfoEsrfError):
+        r.run()
+    torch.cuda.synchronize()
+    side = torch.cuda.Stream()
+    g = torch.cuda.CUDAGraph()
+    with torch.cuda.stream(side):
+        g.capture_begin()
+        try:
+            with pytest.raises(ie.InfoEsrfError):
+                r.run()
+        finally:
+            g.capture_end()
+    torch.cuda.synchronize()
+    # the library still works, the largest accepted class included
+    ok = runner([one, small], 2, n_ritz=0, oversample=0)
+    assert ok.run() == ie.OK
+    torch.cuda.synchronize()
+    want = [x.clone() for x in ok.results()[0]]
+    full = runner([one] + [small] * 2048, 2, n_ritz=0, oversample=0)
+    assert full.run() == ie.OK
+    torch.cuda.synchronize()
+    got = full.results()[0]
+    assert torch.equal(got[0], want[0]) and all(torch.equal(x, want[1]) for x in got[1:])
+    assert np.all(full.stats().converged)
