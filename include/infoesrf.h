@@ -320,14 +320,20 @@ int infoesrf_perturbation_update(const infoesrf_problem* prob, int32_t Q, const 
  * forked onto library-owned streams (default priority) that wait on and join
  * back into `stream` through events (its mean system, at shift 0, joins an
  * instance's perturbation systems); then one persistent launch per kernel
- * shape (instances with m <= 1024, and larger ones) runs every sweep of every
- * instance's systems from a queue (largest instance first, smallest shifts
- * first within it): a workgroup restarts a system from its true FP64 residual
+ * shape (m <= 512, m <= 1024, and larger), each on a stream of its own, the
+ * largest instances' on `stream`, runs every sweep of its instances' systems
+ * from a queue (largest instance first, smallest shifts first within it): a
+ * workgroup restarts a system from its true FP64 residual
  * while that is above rtol, up to the sweep budget (2 for FP64 and 4 for
  * MIXED_FP32 inner applies with host_sync 0, 40 with host_sync 1); then each
  * instance's quadrature sum and final update.  The call makes no host read
  * before the final status when host_sync is 1 and none at all when it is 0
- * (capturable in a HIP graph).
+ * (capturable in a HIP graph).  Where a class is refused the call fails, with
+ * `stream` ordered behind what had been launched.  A host thread keeps a set
+ * of these streams for each of the last four streams it called on, so its
+ * calls on two streams overlap; calls on more streams than that, or captures
+ * on streams it had not called on before, may share a set and then wait for
+ * each other.
  * Otherwise instances run largest first on a pool of library-owned streams
  * (default priority) that fork from and join back into `stream`, each as the
  * single-instance calls.  With host_sync 1 the return code is the most severe

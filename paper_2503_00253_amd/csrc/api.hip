@@ -1778,11 +1778,45 @@ class WorkerPool {
     std::unique_lock<std::mutex> lk(latch.mu);
     latch.cv.wait(lk, [&] { return latch.left == 0; });
   }
-  // Stream idx (< kWorkers) of the calling thread on device dev, created on first use and kept
-  // for the thread's lifetime (default priority, non-blocking).
-  static hipError_t worker_stream(int dev, int idx, hipStream_t* out) {
+  // The calling thread keeps up to kSets sets of streams a device, one for each stream that it makes
+  // batched calls on, so that two such calls on two streams overlap (over one set the second one's set-ups
+  // waited behind the first one's solve: two calls of 8 small filters 2.69 ms together, now 2.41).
+  // Past kSets the oldest stream's set is handed on: the calls that share one then wait for each
+  // other.  A stream that is being captured gets no new set: it takes the first one.
+  static constexpr int kSets = 4;
+  static hipError_t stream_set(int dev, hipStream_t st, int* set) {
+    struct Sets {
+      hipStream_t of[kSets];
+      int n = 0, next = 0;
+    };
+    static thread_local std::vector<Sets> all;
+    if (all.size() <= (size_t)dev) all.resize(dev + 1);
+    Sets& s = all[dev];
+    for (int i = 0; i < s.n; ++i)
+      if (s.of[i] == st) {
+        *set = i;
+        return hipSuccess;
+      }
+    *set = 0;
+    if (st && s.n > 0) {  // the default stream cannot be captured
+      hipStreamCaptureStatus c = hipStreamCaptureStatusNone;
+      const hipError_t e = hipStreamIsCapturing(st, &c);
+      if (e != hipSuccess || c != hipStreamCaptureStatusNone) return e;
+    }
+    if (s.n < kSets) {
+      *set = s.n++;
+    } else {
+      *set = s.next;
+      s.next = (s.next + 1) % kSets;
+    }
+    s.of[*set] = st;
+    return hipSuccess;
+  }
+  // Stream idx (< kWorkers) of a set of the calling thread on device dev, created on first use and
+  // kept for the thread's lifetime (default priority, non-blocking).
+  static hipError_t worker_stream(int dev, int idx, hipStream_t* out, int set = 0) {
     static thread_local std::vector<hipStream_t> streams;
-    const size_t k = (size_t)dev * kWorkers + idx;
+    const size_t k = ((size_t)dev * kSets + set) * kWorkers + idx;
     if (streams.size() <= k) streams.resize(k + 1, nullptr);
     if (!streams[k]) {
       const hipError_t e = hipStreamCreateWithFlags(&streams[k], hipStreamNonBlocking);
@@ -2006,7 +2040,9 @@ int batched_one_launch(const infoesrf_problem* probs, int count, const int32_t* 
   ev.e.assign(3 * (1 + nw), nullptr);  // three times: a fork and the streams' joins
   for (auto& x : ev.e) IE_HIP(hipEventCreateWithFlags(&x, hipEventDisableTiming));
   std::vector<hipStream_t> ws(nw);
-  for (int w = 0; w < nw; ++w) IE_HIP(WorkerPool::worker_stream(dev, w, &ws[w]));
+  int set = 0;
+  IE_HIP(WorkerPool::stream_set(dev, st, &set));
+  for (int w = 0; w < nw; ++w) IE_HIP(WorkerPool::worker_stream(dev, w, &ws[w], set));
   auto fork = [&](int phase) -> int {  // the worker streams wait for `st`
     const hipEvent_t e = ev.e[phase * (1 + nw)];
     IE_HIP(hipEventRecord(e, st));
@@ -2048,7 +2084,8 @@ int batched_one_launch(const infoesrf_problem* probs, int count, const int32_t* 
   // the instance's sweep budget allows, restarts from it at once.  A system that spends its
   // budget stays live and is reported not converged; a further launch would skip it.  Each class
   // has its own stream, so the next one's workgroups take the CUs that the last systems of a
-  // class leave idle.
+  // class leave idle; the first (the largest instances, most of the time) is on the caller's, as
+  // the worker streams' next work may be another call's.
   IE_TRY(fork(1));
   hipError_t refused = hipSuccess;  // of a class: those launched before it are still joined
   if (nl > 0) {
@@ -2066,7 +2103,8 @@ int batched_one_launch(const infoesrf_problem* probs, int count, const int32_t* 
       // the launch writes the table, builds the queue (live systems instance by instance,
       // largest first) and iterates
       refused = launch_pcg_tail_multi(ordered.data(), (int)cl.size(), ba.table + t0, ba.seg + s0, ba.cnt + t0,
-                                      ba.list + s0, ba.words + 2 * c, ba.words + 2 * c + 1, segc, ws[c % nw]);
+                                      ba.list + s0, ba.words + 2 * c, ba.words + 2 * c + 1, segc,
+                                      c ? ws[(c - 1) % nw] : st);
       t0 += (int)cl.size();
       s0 += segc;
     }

@@ -1,5 +1,6 @@
 """What infoesrf_update_batched leaves on the caller's stream: its work is ordered there also where one
-class of instances is refused after another was launched.
+class of instances is refused after another was launched, and calls of one thread on several streams,
+more than the thread keeps stream sets for, do not disturb each other.
 """
 import sys
 
@@ -60,3 +61,42 @@ def test_a_refused_class_leaves_no_stream_behind():
     got = full.results()[0]
     assert torch.equal(got[0], want[0]) and all(torch.equal(x, want[1]) for x in got[1:])
     assert np.all(full.stats().converged)
+
+
+def test_calls_on_several_streams():
+    """Batches of all three kernel shapes, enqueued by one thread on six streams at once, three times
+    over, and one captured on a stream that had no call before: the same bits as alone."""
+    say("several streams")
+    runs, want = [], []
+    for k in range(6):
+        probs = [syn.gaussian_problem(n, 6, 20.0, min(30.0, n / 8), 4, 0.25, 3, 100.0, 50 + 10 * k + n % 7, name="s%d" % n)
+                 for n in (4400, 2400 + 40 * k, 600, 160)]
+        r = runner(probs, 3, n_ritz=4, oversample=4, precision=ie.MIXED_FP32 if k % 2 else ie.FP64)
+        assert r.one_launch() and r.run() == ie.OK
+        torch.cuda.synchronize()
+        runs.append(r)
+        want.append([x.clone() for x in r.outs + r.means])
+    streams = [torch.cuda.Stream() for _ in runs]
+    for rep in range(3):
+        for r in runs:
+            for x in r.outs + r.means:
+                x.fill_(float("nan"))
+        torch.cuda.synchronize()
+        for r, s in zip(runs, streams[rep:] + streams[:rep]):
+            with torch.cuda.stream(s):
+                assert r.run() == ie.OK
+        torch.cuda.synchronize()
+        for r, w in zip(runs, want):
+            assert all(torch.equal(x, y) for x, y in zip(r.outs + r.means, w)), rep
+    g = torch.cuda.CUDAGraph()
+    with torch.cuda.graph(g, stream=torch.cuda.Stream()):
+        runs[0].run()
+    for rep in range(3):
+        for x in runs[0].outs + runs[0].means:
+            x.fill_(float("nan"))
+        with torch.cuda.stream(streams[0]):
+            assert runs[1].run() == ie.OK
+        torch.cuda.synchronize()
+        g.replay()
+        torch.cuda.synchronize()
+        assert all(torch.equal(x, y) for x, y in zip(runs[0].outs + runs[0].means, want[0])), rep
