@@ -26,6 +26,66 @@ __device__ inline float gelu_grad_f(float z) {
   return Phi + z * phi;
 }
 
+// The correlation with FP32 FMAs.  Block: kVX positions (one a lane) x 4 CPW output channels (CPW a
+// wavefront); input window and weight chunk in LDS, the weights read as wave-uniform broadcasts.  It
+// does no work for channels that are not there, so it takes the layers that leave k_conv_mfma's tiles
+// mostly empty (launch_conv_fwd has the rule).  A chunk's sums start at zero and are added to the total.
+constexpr int kVX = 64;
+template <int CPW>
+__global__ __launch_bounds__(256) void k_conv_fma(const float* __restrict__ in, int Cin, const float* __restrict__ W,
+                                                  const float* __restrict__ bias, int Cout, int K, int m,
+                                                  float* __restrict__ pre, float* __restrict__ act, int gelu) {
+  extern __shared__ float sm[];
+  const int h = K / 2;
+  const int WX = kVX + K - 1;
+  float* win = sm;              // kCIC x WX
+  float* wts = sm + kCIC * WX;  // (4 CPW) x kCIC x K
+  const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
+  const int x0 = blockIdx.x * kVX;
+  const int o0 = blockIdx.y * 4 * CPW;
+  const int64_t b = blockIdx.z;
+  const float* inb = in + b * (int64_t)Cin * m;
+  float tot[CPW];
+#pragma unroll
+  for (int j = 0; j < CPW; ++j) tot[j] = 0.f;
+  for (int c0 = 0; c0 < Cin; c0 += kCIC) {
+    const int cc = min(kCIC, Cin - c0);
+    __syncthreads();
+    for (int t = threadIdx.x; t < cc * WX; t += 256) {
+      const int ci = t / WX, u = t % WX;
+      const int x = x0 - h + u;
+      win[t] = (x >= 0 && x < m) ? inb[(int64_t)(c0 + ci) * m + x] : 0.f;
+    }
+    for (int t = threadIdx.x; t < 4 * CPW * cc * K; t += 256) {
+      const int o = t / (cc * K), u = t % (cc * K);
+      wts[o * kCIC * K + u] = o0 + o < Cout ? W[((int64_t)(o0 + o) * Cin + c0) * K + u] : 0.f;
+    }
+    __syncthreads();
+    float acc[CPW];
+#pragma unroll
+    for (int j = 0; j < CPW; ++j) acc[j] = 0.f;
+    for (int ci = 0; ci < cc; ++ci)
+      for (int k = 0; k < K; ++k) {
+        const float v = win[ci * WX + lane + k];
+#pragma unroll
+        for (int j = 0; j < CPW; ++j) acc[j] = fmaf(wts[((wave * CPW + j) * kCIC + ci) * K + k], v, acc[j]);
+      }
+#pragma unroll
+    for (int j = 0; j < CPW; ++j) tot[j] += acc[j];
+  }
+  const int x = x0 + lane;
+  if (x >= m) return;
+#pragma unroll
+  for (int j = 0; j < CPW; ++j) {
+    const int o = o0 + wave * CPW + j;
+    if (o >= Cout) continue;
+    const float z = tot[j] + (bias ? bias[o] : 0.f);
+    const int64_t at = (b * Cout + o) * (int64_t)m + x;
+    if (pre) pre[at] = z;
+    act[at] = gelu ? gelu_f(z) : z;
+  }
+}
+
 // The correlation as an implicit GEMM on FP32 MFMA (v_mfma_f32_16x16x4_f32: FP32 operands and
 // accumulation): output channels x positions, contracted over input channels four at a time and taps.
 // Block: 64 output channels (16 a wavefront) x 32 positions.  Input channels come in chunks of 16 whose
@@ -33,8 +93,10 @@ __device__ inline float gelu_grad_f(float z) {
 // multiplied.  LDS strides: a window row of kWinS = 80 words puts the 16 positions x 4 channels of an
 // operand on 64 banks, a weight row of 16 K + 4 words the 16 outputs x 4 channels (K is odd).  32
 // positions a block, so that the smallest training batches (8 members x 1024 positions) still give one
-// block a CU; the LDS reads (3 words a lane for 2 MFMA) then bound it.  8 members x 1024 positions, 64 x
-// 64 channels, 9 taps (604 MFLOP): 46 us with FP32 FMAs, four output channels a wavefront; 18 us so.
+// block a CU.  The chunk held in registers bounds it: from 9 taps on (256 registers and 44 accumulation
+// registers) one wavefront a SIMD is resident, which has nothing to hide its LDS reads (3 words a lane
+// for 2 MFMA) and its chunk's loads behind.  8 members x 1024 positions, 64 x 64 channels, 9 taps (604
+// MFLOP): 46 us with FP32 FMAs, four output channels a wavefront; 18 us so.
 // FLIP: the weights are those of the layer whose input gradient this is, W (Cin, Cout, K), read as
 // W'[o, c, k] = W[c, o, K - 1 - k] (the input gradient of a "same" correlation is the correlation of
 // the output gradient with W').  dz (nullable): the outputs are multiplied by GELU'(dz).
@@ -452,12 +514,36 @@ hipError_t conv_go(const float* in, int Cin, const float* W, const float* bias, 
   hipLaunchKernelGGL(fn, grid, dim3(256), lds, st, in, Cin, W, bias, Cout, m, pre, act, gelu, dz);
   return hipGetLastError();
 }
+// Where the forward correlation runs on the matrix cores, whose tiles are 64 output channels wide and whose
+// chunks 16 input channels deep, full or not.  The FMA kernel does only the channels that are there, and
+// wins once the chip is full: 640 members x 1024 positions, 9 taps: 1 -> 64 channels 519 us on the matrix
+// cores and 92 with FMAs, 64 -> 4: 1122 / 235, 16 -> 16: 575 / 140, 32 -> 32: 851 / 510; 64 -> 64: 1485 /
+// 1990.  Below that, one or two rounds of blocks on the matrix cores are the shorter chain (8 members, 64
+// -> 64: 21 / 61; 64 -> 4: 16 / 37; 16 members, 32 -> 32 still 21 / 33).  Fewer taps leave the matrix kernel
+// its registers, several wavefronts a SIMD, and its line lies lower: forwards of 320 members with 40 hidden
+// channels 1780 us with MFMA and 1120 with FMAs at 9 taps, of 64 members with 130, one tap, 166 and 430.
+bool conv_on_mfma(int Cin, int Cout, int K, int m, int64_t B) {
+  const int64_t tiles = (Cout + 63) / 64, blocks = B * ((m + kCX - 1) / kCX) * tiles;
+  if (Cin < kCIC) return false;
+  const int fill = K == 1 ? 17 : (K <= 5 ? 32 : (K == 7 ? 40 : 42));  // output channels a tile has to hold
+  if (Cout >= fill * tiles) return true;
+  return blocks <= (K == 1 ? 2048 : (K <= 7 || Cin >= 32 ? 512 : 256));
+}
 }  // namespace
 
 hipError_t launch_conv_fwd(const float* in, int Cin, const float* W, const float* bias, int Cout, int K, int m,
                            int64_t B, float* pre, float* act, int gelu, hipStream_t st, bool flip, const float* dz) {
   if (B <= 0) return hipSuccess;
   if (!in || !W || !act || K < 1 || K > kMaxTaps || (K % 2) == 0) return hipErrorInvalidValue;
+  if (!flip && !dz && !conv_on_mfma(Cin, Cout, K, m, B)) {
+    const unsigned gx = (unsigned)((m + kVX - 1) / kVX);
+    const int cpw = Cout >= 16 ? 4 : 1;
+    const size_t lds = sizeof(float) * ((size_t)kCIC * (kVX + K - 1) + 4 * cpw * kCIC * K);
+    const dim3 grid(gx, (unsigned)((Cout + 4 * cpw - 1) / (4 * cpw)), (unsigned)B);
+    hipLaunchKernelGGL(cpw == 4 ? k_conv_fma<4> : k_conv_fma<1>, grid, dim3(256), lds, st, in, Cin, W, bias, Cout, K, m,
+                       pre, act, gelu);
+    return hipGetLastError();
+  }
   switch (K) {
     case 1: return conv_go<1>(in, Cin, W, bias, Cout, m, B, pre, act, gelu, st, flip, dz);
     case 3: return conv_go<3>(in, Cin, W, bias, Cout, m, B, pre, act, gelu, st, flip, dz);

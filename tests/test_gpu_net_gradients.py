@@ -49,3 +49,12 @@ def test_forward_and_gradients_at_tile_edges(H, K, B, m):
     grads = wr.backward(params, cache, wr.head_grad(gy, phi))
     assert abs(float(loss) - want_loss) < 1e-5 * max(1.0, want_loss)
     assert rel(got.cpu().numpy(), flat(grads)) < 1e-4
+
+
+@pytest.mark.parametrize("H,K,B,m", [(16, 9, 9, 1021), (17, 1, 33, 2049), (24, 9, 40, 500), (31, 5, 40, 433),
+                                     (40, 7, 33, 511), (40, 15, 40, 433), (64, 9, 20, 900), (130, 11, 20, 333)])
+def test_forward_and_gradients_where_layers_leave_the_matrix_cores(H, K, B, m):
+    """Batches past the blocks up to which narrow layers run on the matrix cores: hidden layers and the
+    last one with FP32 FMAs, 16 or 4 output channels a block, 64 positions, the last chunk of input
+    channels not full."""
+    test_forward_and_gradients_at_tile_edges(H, K, B, m)
