@@ -493,17 +493,28 @@ static int band_systems_per_block(const Grid& g, size_t elem, int64_t B) {
   return 8;
 }
 
-// Where the FP64 product runs on the matrix cores.  The window of 16 rows is w + 15 positions, in
-// chunks of 16, so a narrow band leaves them idle work: at w = 79 they are as fast as k_band_apply
-// for 640 systems of 4096 points (71 us a call of the covariance apply against 75) and faster below,
-// at w = 39 slower (67 against 62); k_band_apply needs many systems to fill the chip, and up to 64
-// systems the matrix cores win at any width but the narrowest (16 x 256 points, 7 x 21 stencil, 40
-// systems: 58 us against 77; w = 7: the same).  The window has to fit in LDS (bx < 480) and a
-// stencil row's planes within a buffer's 32-bit offsets.
+// Where the FP64 product runs on the matrix cores.  Their blocks of 64 rows x 16 systems pay for their
+// windows whatever the width (1536 systems of 4096 points: about 75 us and 0.32 us a stencil point, where
+// k_band_apply takes 0.23 us a point over 20), so wide bands are theirs at any size (w = 81, 1536 systems:
+// 0.98 of k_band_apply's time; w = 129: 0.75; w = 319: 0.50), and narrower ones while k_band_apply leaves
+// the chip idle: at w = 65 up to 768 blocks (4096 points, 128 systems: 0.88; 256: 1.06; 1536: 1.15), below
+// that for 17 to 64 systems, which k_band_apply holds in blocks of 32 or 64 (w = 21 and 33, 4096 points,
+// 64 systems, 256 blocks: 0.78, 0.73; 16384 points, 1024 blocks: 1.31, 1.20; several stencil rows, 3 x 23
+// on 128 x 32 points, 512 blocks: 0.70; 5 x 41: 0.94), and for fewer systems where the window is long
+// (one stencil row: w = 51: 0.92, w = 41: 1.05; three rows of 23: 0.87 with 128 blocks, 1.21 with 256).
+// Layers that fill a quarter of a block's rows stay off them (16 points a layer, 64 systems: 1.40).  The window
+// has to fit in LDS (bx < 480) and a stencil row's planes within a buffer's 32-bit offsets.
 bool band_apply_on_mfma(const Grid& g, int64_t ldb, int64_t B) {
   const int w = 2 * g.bx + 1;
-  return (w >= 64 || (w >= 16 && B <= 64)) && mf_lds(g.bx) <= (size_t)kMfMaxLds && g.nx < (1 << 28) &&
-         (w + 16 * (kMfPre + 2)) * ldb * (int64_t)sizeof(double) < (int64_t(1) << 31);
+  if (w < 20 || mf_lds(g.bx) > (size_t)kMfMaxLds || g.nx >= (1 << 28) ||
+      (w + 16 * (kMfPre + 2)) * ldb * (int64_t)sizeof(double) >= (int64_t(1) << 31))
+    return false;
+  if (w >= 80) return true;
+  const int64_t blocks = (int64_t)((g.nx + 63) / 64) * g.nz * ((B + 15) / 16);
+  if (w >= 64) return blocks <= 768;
+  if (B > 64 || g.nx < 24) return false;
+  if (B > 16) return blocks <= (g.bz > 0 ? 512 : 256);
+  return g.bz > 0 ? blocks <= 192 : w >= 48 && blocks <= 256;
 }
 
 hipError_t launch_band_build(Prec prec, const Grid& g, const double* Z, int64_t ldz, int64_t N, void* band,
