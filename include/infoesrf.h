@@ -444,7 +444,8 @@ int infoesrf_warmstart_pairs(const infoesrf_problem* prob, int32_t Q, const doub
  * 64, 128) with HIP events at three batch sizes (the Q N systems, a quarter
  * and a sixteenth of them), and records the fastest per batch-size bucket
  * (>= 256, 64..255, < 64 systems) for grids of this shape.  Later applies on
- * such grids use the recorded choice unless opts->tile_rows forces one.  The
+ * such grids use the recorded choice unless opts->tile_rows forces one (FP64
+ * band products on the matrix cores have one shape and use none).  The
  * band form's results do not depend on the choice (each output keeps its
  * summation order); the operator form's do by rounding only.  Synchronizes
  * the stream.  Workspace: infoesrf_workspace_bytes(prob, Q, opts).

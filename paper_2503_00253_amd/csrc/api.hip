@@ -2523,9 +2523,7 @@ int infoesrf_autotune(const infoesrf_problem* prob, int32_t Q, const infoesrf_op
       seen[bucket] = true;
       int best = 0;
       float best_ms = 0.f;
-      const bool one_shape = band && prec == Prec::F64 && band_apply_on_mfma(g, ldr, B);
       for (int c : cands) {
-        if (one_shape && c != cands[0]) break;
         g_force_choice = c;
         hipError_t e = launch(B);  // warm-up (also sets kernel attributes)
         for (int r = 0; r < 5 && e == hipSuccess; ++r) {

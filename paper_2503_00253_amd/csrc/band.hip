@@ -504,7 +504,7 @@ static int band_systems_per_block(const Grid& g, size_t elem, int64_t B) {
 // (one stencil row: w = 51: 0.92, w = 41: 1.05; three rows of 23: 0.87 with 128 blocks, 1.21 with 256).
 // Layers that fill a quarter of a block's rows stay off them (16 points a layer, 64 systems: 1.40).  The window
 // has to fit in LDS (bx < 480) and a stencil row's planes within a buffer's 32-bit offsets.
-bool band_apply_on_mfma(const Grid& g, int64_t ldb, int64_t B) {
+static bool band_on_mfma(const Grid& g, int64_t ldb, int64_t B) {
   const int w = 2 * g.bx + 1;
   if (w < 20 || mf_lds(g.bx) > (size_t)kMfMaxLds || g.nx >= (1 << 28) ||
       (w + 16 * (kMfPre + 2)) * ldb * (int64_t)sizeof(double) >= (int64_t(1) << 31))
@@ -553,7 +553,9 @@ hipError_t launch_band_apply(Prec prec, const Grid& g, const void* band, int64_t
     const double* b = (const double*)band;
     const double* v = (const double*)V;
     double* t = (double*)T;
-    if (band_apply_on_mfma(g, ldb, B)) return band_apply_mfma(g, b, ldb, v, ldv, vcols, B, Bdev, t, ldt, st, pf, zc);
+    // (the tuner times the block shapes of k_band_apply, for the calls that take it)
+    if (!g_force_choice && band_on_mfma(g, ldb, B))
+      return band_apply_mfma(g, b, ldb, v, ldv, vcols, B, Bdev, t, ldt, st, pf, zc);
     switch (band_systems_per_block(g, sizeof(double), B)) {
       case 64: return band_apply_typed<double, 64>(g, b, ldb, v, ldv, vcols, B, Bdev, t, ldt, st, pf, zc);
       case 32: return band_apply_typed<double, 32>(g, b, ldb, v, ldv, vcols, B, Bdev, t, ldt, st, pf, zc);

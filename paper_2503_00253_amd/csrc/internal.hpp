@@ -339,8 +339,6 @@ hipError_t launch_band_build(Prec prec, const Grid& g, const double* Z, int64_t 
 hipError_t launch_band_apply(Prec prec, const Grid& g, const void* band, int64_t ldb, const void* V, int64_t ldv,
                              int64_t vcols, int64_t B, const int32_t* Bdev, void* T, int64_t ldt, hipStream_t st,
                              const ProfDev* prof = nullptr, int32_t* zero_counter = nullptr);
-// the FP64 product of B systems takes the matrix cores (one block shape: nothing to tune)
-bool band_apply_on_mfma(const Grid& g, int64_t ldb, int64_t B);
 
 // The final state-space apply on a declared observed lattice: P Ht R^{-1/2} u for point
 // observations on the lattice needs, for each state point, only the lattice points inside its
