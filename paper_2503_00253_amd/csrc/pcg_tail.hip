@@ -156,6 +156,18 @@ __host__ __device__ constexpr bool tail_caches_ritz(int P, int RPT, int NT) {
   return P > 0 && RPT * P <= (RPT > 2 ? 8 : 20) && NT < 1024;
 }
 
+// Whether a chunk of the band is 2 FP64 or 4 FP32 entries a row, not twice that, with four rows a thread.
+// Every kernel here spills (the 1024-thread ones have 128 registers), and which length costs less is
+// measured, an update of 128 systems of 2000 (512 threads) or 3200 observations: FP64, P = 20, 512
+// threads 2150 us against 2440 (P = 16 the same, P <= 12 do not spill); FP32, 1024 threads, P = 4: 1236 /
+// 1351, 8: 1957 / 2250, 12: 3512 / 3794, 16: 6246 / 6416, 20: 10030 / 10920, but P = 10: 2863 / 2605 and
+// 0: within 4% either way; FP64, 1024 threads, P = 10: 2782 / 2827, but 8: 2115 / 2057, 12: 3663 / 3534, 16:
+// 6029 / 5706, 20 the same.  Launches over many instances take the long chunks (three instances, FP32, 1024
+// threads, P = 20: 13.5 ms, 14.4 with short ones; P = 10: 4.07, 4.22; P = 4 alone 2.13, 1.74).
+__host__ __device__ constexpr bool tail_short_chunks(int P, int RPT, int NT, bool low, bool multi) {
+  return RPT >= 4 && !multi && (NT >= 1024 ? (low ? P > 0 && P != 10 : P == 10) : !low && P == 20);
+}
+
 // Rows of a thread: pairs of adjacent rows, 2 (tid + NT jj) + b for jj < RPT / 2, b in {0, 1}, so
 // that one 16-byte load brings an entry of the FP64 band for both rows.
 template <int NT>
@@ -404,9 +416,11 @@ __global__ __launch_bounds__(NT) void k_pcg_tail(TailInst one, const TailInst* _
   // against 0.57 ms with 32)
   // With four rows a thread, 4 FP64 entries (8 of the packed FP32 band) a chunk keep eight 16-byte
   // loads in flight per thread; the 512-thread kernels up to P = 12 have the registers for them (at 2
-  // and 4 entries k_pcg_tail<4, 4, 512, float> over many instances took 25.0 ms for 22.3).
-  constexpr int CH = RPT >= 4 ? 4 : 8;
-  constexpr int CHQ = 8;
+  // and 4 entries k_pcg_tail<4, 4, 512, float> over many instances took 25.0 ms for 22.3).  Half that
+  // (tail_short_chunks) is what the kernels with more to spill take.
+  constexpr bool kShort = tail_short_chunks(P, RPT, NT, sizeof(BT) == 4, MULTI);
+  constexpr int CH = kShort ? 2 : (RPT >= 4 ? 4 : 8);
+  constexpr int CHQ = kShort ? 4 : 8;
   // the Ritz vectors of the thread's rows stay in registers when they fit
   constexpr bool kLow = sizeof(BT) == 4;
   constexpr bool kCache = tail_caches_ritz(P, RPT, NT);
