@@ -168,19 +168,8 @@ __device__ inline double obs_rhs_entry(const int32_t* __restrict__ h_ptr, const 
   return row_dot(h_idx, h_w, h_ptr[r], h_ptr[r + 1], n, Z + i * n) / sqrt(r_var[r]);
 }
 
-// rhs[s * ld + r] = dinv_r * sum_e w_e Z[idx_e, i], i = (s - s0) % N
-__global__ void k_obs_rhs(const int32_t* __restrict__ h_ptr, const int32_t* __restrict__ h_idx,
-                          const double* __restrict__ h_w, const double* __restrict__ r_var,
-                          const double* __restrict__ Z, int64_t n, int64_t N, int64_t m, double* __restrict__ rhs,
-                          int64_t ld, int64_t s0, int64_t cnt) {
-  const int64_t t = blockIdx.x * (int64_t)blockDim.x + threadIdx.x;
-  if (t >= m * cnt) return;
-  const int64_t c = t / m, r = t % m;
-  rhs[(s0 + c) * ld + r] = obs_rhs_entry(h_ptr, h_idx, h_w, r_var, Z, n, r, c % N);
-}
-
-// The same for systems 0 .. cnt-1 over the whole ld x spad block: zeros in the padding rows
-// (r >= m) and padding systems (s >= cnt).
+// rhs[s * ld + r] = dinv_r * sum_e w_e Z[idx_e, s % N] for systems 0 .. cnt-1 over the whole ld x spad
+// block: zeros in the padding rows (r >= m) and padding systems (s >= cnt).
 __global__ void k_obs_rhs_padded(const int32_t* __restrict__ h_ptr, const int32_t* __restrict__ h_idx,
                                  const double* __restrict__ h_w, const double* __restrict__ r_var,
                                  const double* __restrict__ Z, int64_t n, int64_t N, int64_t m,
@@ -205,18 +194,15 @@ __global__ __launch_bounds__(64) void k_obs_rhs_rows(const int32_t* __restrict__
   if (c < spad) rhs[c * ld + r] = c < cnt ? v : 0.0;
 }
 
-// R^{-1/2} (y - H mu); WAVE: a wavefront per entry (up to kRowOutputs)
-template <bool WAVE>
+// R^{-1/2} (y - H mu), a wavefront per entry
 __global__ void k_innovation(const int32_t* __restrict__ h_ptr, const int32_t* __restrict__ h_idx,
                              const double* __restrict__ h_w, const double* __restrict__ r_var,
                              const double* __restrict__ y, const double* __restrict__ mu, int64_t m, int64_t n,
                              double* __restrict__ out, int64_t ld, int64_t s) {
-  int64_t r = blockIdx.x * (int64_t)blockDim.x + threadIdx.x;
-  if (WAVE) r /= 64;
+  const int64_t r = (blockIdx.x * (int64_t)blockDim.x + threadIdx.x) / 64;
   if (r >= m) return;
-  const double hm = WAVE ? row_dot_wave(h_idx, h_w, h_ptr[r], h_ptr[r + 1], n, mu)
-                         : row_dot(h_idx, h_w, h_ptr[r], h_ptr[r + 1], n, mu);
-  if (!WAVE || (threadIdx.x & 63) == 63) out[s * ld + r] = (y[r] - hm) / sqrt(r_var[r]);
+  const double hm = row_dot_wave(h_idx, h_w, h_ptr[r], h_ptr[r + 1], n, mu);
+  if ((threadIdx.x & 63) == 63) out[s * ld + r] = (y[r] - hm) / sqrt(r_var[r]);
 }
 
 __device__ inline int32_t wrap_offset(int32_t d, int32_t len, int32_t periodic) {
@@ -262,13 +248,10 @@ __device__ inline int32_t wrap_near(int32_t d, int32_t len, int32_t periodic) {
 }
 
 template <int NT>
-__global__ __launch_bounds__(NT) void k_diag_S(const int32_t* __restrict__ h_ptr,
-                                                         const int32_t* __restrict__ h_idx,
-                                                         const double* __restrict__ h_w,
-                                                         const double* __restrict__ r_var,
-                                                         const double* __restrict__ Z, int64_t n, int64_t N,
-                                                         Grid g, const double* __restrict__ dense_L,
-                                                         double* __restrict__ diagS) {
+__global__ __launch_bounds__(NT) void k_diag_S(const int32_t* __restrict__ h_ptr, const int32_t* __restrict__ h_idx,
+                                               const double* __restrict__ h_w, const double* __restrict__ r_var,
+                                               const double* __restrict__ Z, int64_t n, int64_t N, Grid g,
+                                               const double* __restrict__ dense_L, double* __restrict__ diagS) {
   __shared__ double zs[kDiagStage];
   __shared__ double part[NT / 64];
   __shared__ double sw[kDiagRow];
@@ -495,23 +478,11 @@ hipError_t launch_obs_rhs_padded(const int32_t* h_ptr, const int32_t* h_idx, con
   return hipGetLastError();
 }
 
-hipError_t launch_obs_rhs(const int32_t* h_ptr, const int32_t* h_idx, const double* h_w, const double* r_var,
-                          const double* Z, int64_t n, int64_t N, int64_t m, double* rhs, int64_t ld, int64_t s0,
-                          int64_t cnt, hipStream_t st) {
-  hipLaunchKernelGGL(k_obs_rhs, dim3(blocks_for(m * cnt)), dim3(kBlock), 0, st, h_ptr, h_idx, h_w, r_var, Z, n, N,
-                     m, rhs, ld, s0, cnt);
-  return hipGetLastError();
-}
-
 hipError_t launch_innovation(const int32_t* h_ptr, const int32_t* h_idx, const double* h_w, const double* r_var,
                              const double* y, const double* mu, int64_t m, int64_t n, double* out, int64_t ld,
                              int64_t s, hipStream_t st) {
-  if (m <= kRowOutputs)
-    hipLaunchKernelGGL(k_innovation<true>, dim3(blocks_for(64 * m)), dim3(kBlock), 0, st, h_ptr, h_idx, h_w, r_var, y,
-                       mu, m, n, out, ld, s);
-  else
-    hipLaunchKernelGGL(k_innovation<false>, dim3(blocks_for(m)), dim3(kBlock), 0, st, h_ptr, h_idx, h_w, r_var, y, mu,
-                       m, n, out, ld, s);
+  hipLaunchKernelGGL(k_innovation, dim3(blocks_for(64 * m)), dim3(kBlock), 0, st, h_ptr, h_idx, h_w, r_var, y, mu, m, n,
+                     out, ld, s);
   return hipGetLastError();
 }
 

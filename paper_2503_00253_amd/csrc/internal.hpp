@@ -200,7 +200,8 @@ __device__ inline double row_dot_shared(const int32_t* __restrict__ h_idx, const
 }
 
 // The same chain for one sum by a wavefront: its lanes bring the products' factors 64 at a time, every
-// lane adds them in order (a thread alone 21 us for 177 entries, 13 so).
+// lane adds them in order (a thread alone 21 us for 177 entries, 13 so; rows of one or two entries 1.8
+// and 3.1, so each lane forms those itself).
 __device__ inline double row_dot_wave(const int32_t* __restrict__ h_idx, const double* __restrict__ h_w, int32_t e0,
                                       int32_t e1, int64_t n, const double* __restrict__ col) {
   auto from = [](double x, int l) {
@@ -209,6 +210,7 @@ __device__ inline double row_dot_wave(const int32_t* __restrict__ h_idx, const d
     const int hi = __builtin_amdgcn_readlane((int)(b >> 32), l);
     return __builtin_bit_cast(double, ((long long)hi << 32) | (unsigned)lo);
   };
+  if (e1 - e0 <= 2) return row_dot(h_idx, h_w, e0, e1, n, col);
   double a = 0.0;
   for (int32_t c0 = e0; c0 < e1; c0 += 64) {
     const int32_t e = min(c0 + (int32_t)(threadIdx.x & 63), e1 - 1);
@@ -245,13 +247,8 @@ hipError_t launch_csc_finish(const int32_t* h_ptr, const int32_t* h_idx, const d
                              int32_t* col_cnt, int32_t* col_ptr, int32_t* row_of, double* w_of, int32_t* flags,
                              hipStream_t st);
 
-// rhs[s * ld + r] = dinv[r] * sum_e h_w[e] * Z[h_idx[e], member(s)] for systems s in [s0, s0+cnt),
-// member(s) = (s - s0) % N.
-hipError_t launch_obs_rhs(const int32_t* h_ptr, const int32_t* h_idx, const double* h_w, const double* r_var,
-                          const double* Z, int64_t n, int64_t N, int64_t m, double* rhs, int64_t ld, int64_t s0,
-                          int64_t cnt, hipStream_t st);
-// The same for systems 0 .. cnt-1, writing the whole ld x spad block (zeros past m rows and past
-// cnt systems).
+// rhs[s * ld + r] = dinv[r] * sum_e h_w[e] * Z[h_idx[e], s % N] for systems 0 .. cnt-1, writing the
+// whole ld x spad block (zeros past m rows and past cnt systems).
 hipError_t launch_obs_rhs_padded(const int32_t* h_ptr, const int32_t* h_idx, const double* h_w, const double* r_var,
                                  const double* Z, int64_t n, int64_t N, int64_t m, double* rhs, int64_t ld,
                                  int64_t cnt, int64_t spad, hipStream_t st);

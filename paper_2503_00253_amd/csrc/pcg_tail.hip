@@ -195,7 +195,7 @@ __device__ inline float4 tail_ld16f(__amdgpu_buffer_rsrc_t rs, uint32_t voff, ui
 // once for the two.
 
 // (RPT: the rows the wavefront applies, one pair or two.)
-template <int RPT, int NT, int CH, bool ADJ>
+template <int RPT, int CH, bool ADJ>
 __device__ inline void tail_apply_rows(__amdgpu_buffer_rsrc_t rsA, uint32_t colA, const uint32_t* roff,
                                        const int* corner, const double* sp, int hh, int ww, int Wp, double* qv) {
 #pragma unroll
@@ -270,7 +270,7 @@ __device__ inline void tail_apply_rows(__amdgpu_buffer_rsrc_t rsA, uint32_t colA
 // entry holds finite values (the next lattice row, or the zeroed slack after the padded lattice),
 // which the zero weights cancel.  CH entries a chunk (a multiple of 4); the sums are in FP64.
 // CHAIN: the last quads join the chain of the sums; otherwise each is summed apart and added.
-template <int RPT, int NT, int CH, bool ADJ, bool CHAIN>
+template <int RPT, int CH, bool ADJ, bool CHAIN>
 __device__ inline void tail_apply_rows_q(__amdgpu_buffer_rsrc_t rsQ, uint32_t colQ, const uint32_t* rowq,
                                          const int* corner, const double* sp, int hh, int ww4, int Wp,
                                          double* qv) {
@@ -295,7 +295,7 @@ __device__ inline void tail_apply_rows_q(__amdgpu_buffer_rsrc_t rsQ, uint32_t co
         // the pair's shared window (CH + 1 entries from an even index) in 16-byte LDS reads
 #pragma unroll
         for (int jj = 0; jj < RPT / 2; ++jj) {
-            const double* pw = sp + corner[2 * jj] + lrow + d0;
+          const double* pw = sp + corner[2 * jj] + lrow + d0;
           double w[CH + 1];
 #pragma unroll
           for (int i = 0; i < CH / 2; ++i) {
@@ -615,12 +615,12 @@ __global__ __launch_bounds__(NT) void k_pcg_tail(TailInst one, const TailInst* _
 #pragma unroll
         for (int jj = R; jj < RPT; ++jj) qv[jj] = 0.0;
         if (!kLow || fp64) {
-          if (adj) tail_apply_rows<R, NT, CH, true>(rsA, colA, roff, corner, sp, hh, ww, Wp, qv);
-          else tail_apply_rows<R, NT, CH, false>(rsA, colA, roff, corner, sp, hh, ww, Wp, qv);
+          if (adj) tail_apply_rows<R, CH, true>(rsA, colA, roff, corner, sp, hh, ww, Wp, qv);
+          else tail_apply_rows<R, CH, false>(rsA, colA, roff, corner, sp, hh, ww, Wp, qv);
         } else {
           const int ww4 = (ww + 3) & ~3;
-          if (adj) tail_apply_rows_q<R, NT, CHQ, true, (RPT > 2)>(rsI, colI, roffI, corner, sp, hh, ww4, Wp, qv);
-          else tail_apply_rows_q<R, NT, CHQ, false, (RPT > 2)>(rsI, colI, roffI, corner, sp, hh, ww4, Wp, qv);
+          if (adj) tail_apply_rows_q<R, CHQ, true, (RPT > 2)>(rsI, colI, roffI, corner, sp, hh, ww4, Wp, qv);
+          else tail_apply_rows_q<R, CHQ, false, (RPT > 2)>(rsI, colI, roffI, corner, sp, hh, ww4, Wp, qv);
         }
       };
       static_assert(RPT <= 4, "at most two pairs a thread");
