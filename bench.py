@@ -34,7 +34,7 @@ PEAK_L2_GBS = 256 * 64 * 2.4
 DTYPE = {0: "f64", 1: "f32/f64", 2: "bf16/f64"}
 # profile slots of the covariance applies: (kernel, bound, MFMA peak key)
 SLOTS = {0: ("k_cov_stencil<fp64>", "mfma", 0), 1: ("k_cov_stencil<fp32>", "mfma", 1),
-         2: ("k_cov_bf16", "mfma", 2), 3: ("k_band_apply<fp64>", "hbm", None),
+         2: ("k_cov_bf16", "mfma", 2), 3: ("k_band_apply(_mfma)<fp64>", "hbm", None),
          4: ("k_band_apply<fp32>", "hbm", None), 5: ("k_pcg_fused", "hbm", None),
          6: ("k_pcg_tail", "alu", None)}
 SOLVERS = {"plain": 0, "compact": 1, "multishift": 3, "block": 4}

@@ -200,8 +200,9 @@ __device__ inline double row_dot_shared(const int32_t* __restrict__ h_idx, const
 }
 
 // The same chain for one sum by a wavefront: its lanes bring the products' factors 64 at a time, every
-// lane adds them in order (a thread alone 21 us for 177 entries, 13 so; rows of one or two entries 1.8
-// and 3.1, so each lane forms those itself).
+// lane adds them in order (a thread alone 21 us for 177 entries, 13 so).  Rows of one or two entries each
+// lane forms itself (100 rows of one: 3.1 us through the chain, 2.8 so; 1.9 with a thread a row, whose
+// one block starts sooner than 25).
 __device__ inline double row_dot_wave(const int32_t* __restrict__ h_idx, const double* __restrict__ h_w, int32_t e0,
                                       int32_t e1, int64_t n, const double* __restrict__ col) {
   auto from = [](double x, int l) {

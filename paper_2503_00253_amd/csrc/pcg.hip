@@ -227,8 +227,11 @@ __global__ __launch_bounds__(256) void k_pcg_fused(PCGState st, LMP lmp, int mod
   // The Ritz vectors are read for the dots of r and, when they fit in registers, kept for the
   // preconditioned residual, so each system reads them once per iteration.  (They are not loaded
   // with the system's data: that many loads in flight would stall the first round trip.)
-  // (With the 2 P + 1 sums they have to leave two wavefronts a SIMD: 4096 points, 1024 observations, 10
-  // Ritz pairs 16.5 us a launch with a second read, 14.5 without.)
+  // (With the 2 P + 1 sums they have to leave two wavefronts a SIMD.  A launch with a second read and
+  // without: 1000 observations, 8 Ritz pairs, 640 systems at first 19.9 / 18.2 us in FP64, 18.0 / 16.9 with
+  // FP32 applies, 2016 systems 30.9 / 29.8 and 28.8 / 27.6; 10 pairs 20.9 / 19.3, 2016 systems 33.3 / 31.4;
+  // 400 observations, 16 pairs 17.3 / 16.4, 2016 systems 27.7 / 27.4.  Eight rows a thread, 8 pairs: they
+  // do not fit.)
   constexpr bool kCache = RPT * P <= 24 || (RPT <= 4 && RPT * P + P <= 50);
   constexpr int kC = (kCache && P > 0) ? RPT * P : 1;
   double ph[kC], sph[kC];
