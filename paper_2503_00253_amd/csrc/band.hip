@@ -502,16 +502,19 @@ static int band_systems_per_block(const Grid& g, size_t elem, int64_t B) {
 // 64 systems, 256 blocks: 0.78, 0.73; 16384 points, 1024 blocks: 1.31, 1.20; several stencil rows, 3 x 23
 // on 128 x 32 points, 512 blocks: 0.70; 5 x 41: 0.94), and for fewer systems where the window is long
 // (one stencil row: w = 51: 0.92, w = 41: 1.05; three rows of 23: 0.87 with 128 blocks, 1.21 with 256).
+// Where B only bounds a count on the device (at_most: the solver's loop), few of the systems are live most
+// of the time, in k_band_apply's blocks of 64 on too few CUs: w = 71 and 79, 2600 points, 640 systems,
+// a whole update 3.28 and 3.42 ms without the matrix cores, 3.06 and 3.15 with, 3.23 and 3.25 by blocks.
 // Layers that fill a quarter of a block's rows stay off them (16 points a layer, 64 systems: 1.40).  The window
 // has to fit in LDS (bx < 480) and a stencil row's planes within a buffer's 32-bit offsets.
-static bool band_on_mfma(const Grid& g, int64_t ldb, int64_t B) {
+static bool band_on_mfma(const Grid& g, int64_t ldb, int64_t B, bool at_most) {
   const int w = 2 * g.bx + 1;
   if (w < 20 || mf_lds(g.bx) > (size_t)kMfMaxLds || g.nx >= (1 << 28) ||
       (w + 16 * (kMfPre + 2)) * ldb * (int64_t)sizeof(double) >= (int64_t(1) << 31))
     return false;
   if (w >= 80) return true;
   const int64_t blocks = (int64_t)((g.nx + 63) / 64) * g.nz * ((B + 15) / 16);
-  if (w >= 64) return blocks <= 768;
+  if (w >= 64) return at_most || blocks <= 768;
   if (B > 64 || g.nx < 24) return false;
   if (B > 16) return blocks <= (g.bz > 0 ? 512 : 256);
   return g.bz > 0 ? blocks <= 192 : w >= 48 && blocks <= 256;
@@ -554,7 +557,7 @@ hipError_t launch_band_apply(Prec prec, const Grid& g, const void* band, int64_t
     const double* v = (const double*)V;
     double* t = (double*)T;
     // (the tuner times the block shapes of k_band_apply, for the calls that take it)
-    if (!g_force_choice && band_on_mfma(g, ldb, B))
+    if (!g_force_choice && band_on_mfma(g, ldb, B, Bdev != nullptr))
       return band_apply_mfma(g, b, ldb, v, ldv, vcols, B, Bdev, t, ldt, st, pf, zc);
     switch (band_systems_per_block(g, sizeof(double), B)) {
       case 64: return band_apply_typed<double, 64>(g, b, ldb, v, ldv, vcols, B, Bdev, t, ldt, st, pf, zc);
