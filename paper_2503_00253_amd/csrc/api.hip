@@ -1904,7 +1904,8 @@ int perturbation_solve(const infoesrf_problem* prob, int32_t Q, const double* s_
 // at shift 0, all in one plan) in one persistent launch per kernel shape (Sec. 3.2: the (q, i) systems
 // are independent).  Set-up per instance over the worker streams, then per shape the queue over its
 // instances' live systems and the launch, then per instance, over the worker streams again, the
-// quadrature sum, the final update and the counters.  Taken when every instance's inner solve can run in the persistent kernel.
+// quadrature sum, the final update and the counters.  Taken when every instance's inner solve can run in
+// the persistent kernel.
 
 // Workspace of one instance on this path (its mean system included).
 size_t combined_ws_bytes(const infoesrf_problem* P, int32_t Q, const infoesrf_opts* o) {

@@ -180,8 +180,8 @@ hipError_t launch_scatter_unit_obs(const int32_t* h_ptr, const int32_t* h_idx, c
                                    const double* r_var, int64_t n, int64_t j0, int64_t bc, double* V, int64_t ldv,
                                    hipStream_t st) {
   if (bc <= 0) return hipSuccess;
-  hipLaunchKernelGGL(k_scatter_unit_obs, dim3((unsigned)((bc + 3) / 4)), dim3(256), 0, st, h_ptr, h_idx, h_w, r_var, n, j0, bc,
-                     V, ldv);
+  hipLaunchKernelGGL(k_scatter_unit_obs, dim3((unsigned)((bc + 3) / 4)), dim3(256), 0, st, h_ptr, h_idx, h_w, r_var, n,
+                     j0, bc, V, ldv);
   return hipGetLastError();
 }
 

@@ -38,9 +38,9 @@ int net_forward(const Net& n, const float* X, int64_t B, int64_t m, float* Y, vo
 int net_forward_bf16(const Net& n, const float* X, int64_t B, int64_t m, float* Y, void* ws, size_t ws_bytes,
                      hipStream_t st);
 
-// The "same" correlation with W (Cout, Cin, K) in FP32, on MFMA or with FMAs (narrow layers); pre (nullable) keeps the values before
-// GELU.  flip: W is (Cin, Cout, K), applied as W'[o, c, k] = W[c, o, K - 1 - k] (the input gradient);
-// dz (nullable): outputs times GELU'(dz).
+// The "same" correlation with W (Cout, Cin, K) in FP32, on MFMA or with FMAs (narrow layers); pre
+// (nullable) keeps the values before GELU.  flip: W is (Cin, Cout, K), applied as W'[o, c, k] =
+// W[c, o, K - 1 - k] (the input gradient); dz (nullable): outputs times GELU'(dz).
 hipError_t launch_conv_fwd(const float* in, int Cin, const float* W, const float* bias, int Cout, int K, int m,
                            int64_t B, float* pre, float* act, int gelu, hipStream_t st, bool flip = false,
                            const float* dz = nullptr);
